@@ -730,6 +730,7 @@ struct EpArgs {
   int H, Hkv, hd;
   const int* pos;        // [R] rotary position of each row
   const float2* rope;    // [max_ctx][hd / 2] (cos, sin)
+  unsigned rope_bytes;   // its size (positions past it, as in rows that nothing has staged, read as zeros)
   const int* rowslot;    // [R] KV-pool slot
   void* q;               // [R][H][hd]
   void* kv_layer;        // this layer's KV pool (null: no K/V stores, for timing)
@@ -853,7 +854,7 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_ep_kernel(EpArgs a) {
       const int f4 = 4 * (rl >> 4);
       if (EPI == EP_ROPE) {
         const int i0 = 16 * (item_of(k) % hp);                // the pair's first feature in the head
-        const auto cr = make_rsrc(a.rope, (unsigned)0x7fffffff);
+        const auto cr = make_rsrc(a.rope, a.rope_bytes);
         const int r0 = (int)(threadIdx.x >> 4), j = (int)(threadIdx.x & 15);
         cs0 = bload64<0>(cr, r0 < T ? (unsigned)(((size_t)spos[r0] * (a.hd / 2) + i0 + j) * 8) : OOB);
         if (MTV == 2)
@@ -2655,7 +2656,8 @@ static hipError_t forward_t(const Model& m, const Work& w, const Step& s, Prof* 
       EpArgs qa{};
       qa.w = lp.wqkv; qa.x = w.xbuf; qa.S = Sd; qa.n_tiles = qkvN / 16; qa.n_items = qkvN / 32;
       qa.ssq = w.ssq; qa.d = d; qa.eps = m.eps;
-      qa.H = m.H; qa.Hkv = m.Hkv; qa.hd = m.hd; qa.pos = w.pos; qa.rope = m.rope; qa.rowslot = w.slot;
+      qa.H = m.H; qa.Hkv = m.Hkv; qa.hd = m.hd; qa.pos = w.pos; qa.rope = m.rope;
+      qa.rope_bytes = (unsigned)((size_t)m.max_ctx * (m.hd / 2) * 8); qa.rowslot = w.slot;
       qa.q = w.q; qa.kv_layer = kvl; qa.kv_cap = s.cap ? (void*)(s.cap + (size_t)l * c_layer + c_k) : nullptr;
       if ((e = timed(prof, PC_QKV, st, [&] { return gemm_ep<DT, EP_ROPE>(qa, R, st); })) != hipSuccess) return e;
     } else {
@@ -2888,6 +2890,7 @@ hipError_t run_gemm_sequence(const Model& m, const Work& w, int which, int R, hi
       // no K/V stores (the staged slots may hold committed rows)
       ea.w = lp.wqkv; ea.x = w.xbuf; ea.S = d / ks; ea.n_tiles = qkvN / 16; ea.n_items = qkvN / 32;
       ea.ssq = w.ssq; ea.H = m.H; ea.Hkv = m.Hkv; ea.hd = m.hd; ea.pos = w.pos; ea.rope = m.rope;
+      ea.rope_bytes = (unsigned)((size_t)m.max_ctx * (m.hd / 2) * 8);
       ea.rowslot = w.slot; ea.q = w.q;
     } else if (which == PC_OPROJ) {
       ea.w = lp.wo; ea.x = w.xbuf; ea.S = qdim / ks; ea.n_tiles = d / 16; ea.n_items = d / 16;

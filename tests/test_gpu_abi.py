@@ -126,3 +126,15 @@ def test_load_kv_round_trip_errors_and_parity(ee, eng):
     np.testing.assert_allclose(eng.logits(), ref.last_logits, rtol=0, atol=1e-4)
     assert (a, nxt) == (ra, rn)
     eng.rollback(1, 0, -1)
+
+
+@pytest.mark.parametrize("fill", [0x00, 0x41, 0xc1])
+def test_time_gemm_on_rows_nothing_has_staged(ee, fill):
+    # the staged positions of rows no block has run hold whatever the workspace held: the rotary
+    # table is read within its size
+    shape = get_shape("tiny")
+    e = ee.Engine(shape, gen_weights(shape, seed=9, std=0.1), max_ctx=200, max_seqs=1, k_max=64)
+    e.workspace.fill_(fill)
+    for cls in ("qkv", "oproj", "gateup", "down", "lmhead"):
+        assert e.time_gemm(cls, 65, 1) > 0.0
+    e.close()
