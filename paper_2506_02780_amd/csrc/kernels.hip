@@ -436,6 +436,9 @@ __device__ __forceinline__ float row_scale(const float* __restrict__ ssq, int t,
 constexpr int FK_MAX_S = 128;   // super-steps one workgroup reduces (16 per wave)
 constexpr int FK_GROUP = 32;    // rows of a group held in registers
 
+// epilogues of the one-slice projections (SWIGLU: gemm_swiglu_kernel and gemm_wide_kernel)
+enum { EP_ROPE = 1, EP_RESID = 2, EP_STORE = 3, EP_SWIGLU = 4 };
+
 __host__ __device__ inline int fk_groups(int R) { return R <= FK_GROUP + 1 ? 1 : (R - 1 + FK_GROUP - 1) / FK_GROUP; }
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + expf(-g)) * u; }
@@ -663,12 +666,33 @@ static void launch_gemm_swiglu(const FkArgs& a, int spw, dim3 grid, hipStream_t 
   }
 }
 
+// Whether a block of R rows runs a one-slice projection of S super-steps as
+// gemm_wide_kernel: from three 32-row groups on (66 rows).  Measured inside
+// 7B steps (S = 128; us per launch, 32-row groups -> wide): at 513 rows
+// gate/up 221 -> 152, QKV 80 -> 54, O 53 -> 45, LM head 321 -> 189; at 96 rows
+// 52.5 -> 44, 25 -> 23, 16.7 -> 16, 78 -> 58.  At 65 rows two groups still
+// stream cold weights near the HBM rate: the K = 64 step takes 560 us with the
+// group kernels and 565-577 with QKV and the LM head wide.  At the 1B width
+// (S = 64) a task's fixed cost weighs more: launched back to back, the LM head
+// takes 32 -> 24 us at 65 rows and QKV 10.4 -> 9.6 at 66, but O 7.2 -> 8.0 and
+// gate/up 21.2 -> 21.7 at 129 (10.4 -> 8.1 and 34 -> 32 at 257), so these two
+// change over at 193.  Results do not depend on the choice.
+inline bool wide_block(int R, int S, int epi) {
+  if (S > 64 || epi == EP_ROPE || epi == EP_STORE) return R > 2 * FK_GROUP + 1;
+  return R > 192;
+}
+template <int DT>
+static hipError_t gemm_swiglu_wide(const uint4* wgu, const uint4* x, int F, int d, int R, void* z, float* ssq,
+                                   const float* ssqt, float eps, hipStream_t st);
+
 // z = silu(r x Wg^T) * (r x Wu^T) for R rows (r: each row's norm scale, from
 // 1024-column chunk sums ssq, or from 16-column tile sums ssqt when given),
 // when d / KS <= FK_MAX_S.
+// ssq: the 1024-column chunk sums, or (ssqt given) scratch of at least R floats.
 template <int DT>
-static hipError_t gemm_swiglu(const uint4* wgu, const uint4* x, int F, int d, int R, void* z, const float* ssq,
+static hipError_t gemm_swiglu(const uint4* wgu, const uint4* x, int F, int d, int R, void* z, float* ssq,
                               const float* ssqt, float eps, hipStream_t st) {
+  if (wide_block(R, d / Geo<DT>::KS, EP_SWIGLU)) return gemm_swiglu_wide<DT>(wgu, x, F, d, R, z, ssq, ssqt, eps, st);
   FkArgs a;
   a.w = wgu; a.x = x; a.z = z;
   a.ssq = ssq; a.ssqt = ssqt; a.d = d; a.eps = eps;
@@ -715,8 +739,6 @@ inline bool fused_swiglu(int d, int dt) { return d / ks_of(dt) <= FK_MAX_S; }
 //   * EP_STORE (LM head): single tiles, the fp32 products stored as they are
 //     (logits_kernel applies the final norm's row scale).
 // Each output's reduction order depends only on K, never on the block's rows.
-
-enum { EP_ROPE = 1, EP_RESID = 2, EP_STORE = 3 };
 
 struct EpArgs {
   const uint4* w;        // packed weights [n_tiles][S][64]
@@ -1042,12 +1064,374 @@ static void launch_gemm_ep(const EpArgs& a, int spw, dim3 grid, hipStream_t st) 
   }
 }
 
+// ------------------------------------------------------------ wide blocks --
+//
+// The one-slice projections (QKV, O, gate/up, LM head) of blocks with many
+// rows: long drafts, prompts, batches.  The kernels above hold a 32-row group
+// in registers and take every weight tile in again for each group, so with
+// many groups the L2-to-CU traffic bounds them.  Here a workgroup owns a tile
+// of MT row tiles x NT feature tiles and streams both operands: wave w holds
+// the whole tile's accumulators for chain w (super-steps w, w + 8, ...), so
+// each loaded fragment serves MT or NT matrix instructions, and operands need
+// neither LDS nor a barrier.  NTW: non-temporal weight loads (one row group:
+// nothing re-reads them; LM head 60.8 -> 57.4, gate/up 43.7 -> 42.2 us at 96
+// rows; with two groups QKV 23.0 -> 28.4).  The eight chains are added in wave order through
+// LDS: the arithmetic of the kernels above, so a row's result does not depend
+// on which of them computed it.
+
+struct WideArgs {
+  EpArgs e;             // operands and the epilogue's arguments
+  int ng, ntask;        // row groups; tasks = row groups x feature groups
+  void* z;              // SWIGLU: packed [R, F] activations of the down projection
+  int z_S;
+  const float* rs;      // SWIGLU: row scales [R], or null: from the chunk sums
+};
+
+template <int DT, int MT, int NT, int EPI, bool NTW>
+__global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) {
+  constexpr int W = GEMM_WAVES;
+  constexpr int ESZ = Geo<DT>::ESZ;
+  constexpr bool PAIRS = EPI == EP_ROPE || EPI == EP_SWIGLU;
+  static_assert(NT % 2 == 0 && MT <= W, "two feature tiles per reduction round, one wave per row tile");
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 15, grp = lane >> 4;
+  const int S = a.e.S, R = a.e.R, nrt = (R + 15) / 16, n_tiles = a.e.n_tiles;
+  const int hp = EPI == EP_ROPE ? a.e.hd / 32 : 1, th = 2 * hp;
+  const auto xs = make_rsrc(a.e.x, (unsigned)((size_t)nrt * S * 1024));
+  const auto ws = make_rsrc(a.e.w, (unsigned)((size_t)n_tiles * S * 1024));
+  __shared__ f32x4 red[W][2 * MT][64];
+
+  // workgroups are dealt to the 8 XCDs in turn: an XCD's workgroups walk one
+  // contiguous eighth of the tasks, the row groups of a feature group next to
+  // each other, so its weights come from HBM once and then from that L2
+  const int per = (a.ntask + 7) / 8, t0 = (int)(blockIdx.x & 7) * per, t1 = min(a.ntask, t0 + per);
+  const int stride = gridDim.x >> 3, first = t0 + (int)(blockIdx.x >> 3);
+  if (first >= t1) return;
+  auto decode = [&](int task, int& rg, int& fg) {
+    fg = task / a.ng;
+    rg = task - fg * a.ng;
+  };
+  struct It {
+    int task, i;   // task, step of the chain
+  };
+  const int steps = (S + W - 1) / W;
+  It L{first, 0}, C{first, 0};
+  unsigned xo[MT], wo[NT];   // byte offsets of the load task's row and feature tiles
+  auto task_offsets = [&](int task) {
+    int rg, fg;
+    decode(task, rg, fg);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) xo[m] = (unsigned)(min(rg * MT + m, nrt - 1) * S) * 1024u;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      int t;
+      if (PAIRS) {
+        const int p = min(fg * (NT / 2) + n / 2, a.e.n_items - 1);
+        t = EPI == EP_ROPE ? (p / hp) * th + p % hp + (n & 1) * hp : p + (n & 1) * a.e.n_items;
+      } else {
+        t = min(fg * NT + n, n_tiles - 1);
+      }
+      wo[n] = (unsigned)(t * S) * 1024u;
+    }
+  };
+  task_offsets(L.task);
+  uint4 xb[2][MT], wb[2][NT];
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // requests the load position's fragments (zeros past the chain or the last task) and moves it on
+  auto load = [&](uint4 (&xf)[MT], uint4 (&wf)[NT]) {
+    const int sl = wv + W * L.i;
+    const unsigned vo = (L.task < t1 && sl < S) ? (unsigned)lane * 16u : OOB;
+    const unsigned so = (unsigned)sl * 1024u;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(ws, vo, wo[n] + so, NTW ? 2 : 0);
+      wf[n] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(xs, vo, xo[m] + so, 0);
+      xf[m] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+    if (++L.i == steps) {
+      L.i = 0;
+      L.task += stride;
+      if (L.task < t1) task_offsets(L.task);
+    }
+  };
+
+  // epilogue of row tile m = wave, reduction round r: v[0], v[1] = the two
+  // feature tiles' products for row row0 + c, features 4 grp .. + 3
+  auto epilogue = [&](int rg, int fg, int r, const f32x4 (&v)[2]) {
+    const int row = (rg * MT + wv) * 16 + c;
+    const bool rok = row < R;
+    if (PAIRS) {
+      const int p = fg * (NT / 2) + r;
+      if (p >= a.e.n_items) return;
+      if (EPI == EP_SWIGLU) {
+        if (!rok) return;
+        const float rs = a.rs ? a.rs[row] : row_scale(a.e.ssq, row, a.e.d, a.e.eps);
+        float zv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) zv[q] = silu_mul(v[0][q] * rs, v[1][q] * rs);
+        const size_t fi = frag_index<DT>(row, 16 * p + 4 * grp, a.z_S);
+        if (DT == DT_BF16)
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.z) + fi) =
+              make_uint2(f2bf_bits(zv[0]) | (f2bf_bits(zv[1]) << 16), f2bf_bits(zv[2]) | (f2bf_bits(zv[3]) << 16));
+        else
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.z) + fi) = make_float4(zv[0], zv[1], zv[2], zv[3]);
+        return;
+      }
+      if (!rok) return;
+      const int head = p / hp, i0 = 16 * (p % hp) + 4 * grp, half = a.e.hd / 2;
+      const float rs = row_scale(a.e.ssq, row, a.e.d, a.e.eps);
+      float y1[4], y2[4];
+      if (head < a.e.H + a.e.Hkv) {
+        const auto cr = make_rsrc(a.e.rope, a.e.rope_bytes);
+        const unsigned co = (unsigned)(((size_t)a.e.pos[row] * half + i0) * 8);
+        const uint4 u0 = bload<0>(cr, co), u1 = bload<0>(cr, co + 16);
+        const float cs[8] = {__uint_as_float(u0.x), __uint_as_float(u0.y), __uint_as_float(u0.z), __uint_as_float(u0.w),
+                             __uint_as_float(u1.x), __uint_as_float(u1.y), __uint_as_float(u1.z), __uint_as_float(u1.w)};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float x1 = v[0][q] * rs, x2 = v[1][q] * rs;
+          y1[q] = fmaf(x1, cs[2 * q], -(x2 * cs[2 * q + 1]));   // (fixed contraction)
+          y2[q] = fmaf(x2, cs[2 * q], x1 * cs[2 * q + 1]);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          y1[q] = v[0][q] * rs;
+          y2[q] = v[1][q] * rs;
+        }
+      }
+      auto put4 = [&](void* base, size_t e, const float* y) {
+        if (DT == DT_BF16)
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(base) + e) =
+              make_uint2(f2bf_bits(y[0]) | (f2bf_bits(y[1]) << 16), f2bf_bits(y[2]) | (f2bf_bits(y[3]) << 16));
+        else
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(base) + e) = make_float4(y[0], y[1], y[2], y[3]);
+      };
+      if (head < a.e.H) {
+        const size_t qb = ((size_t)row * a.e.H + head) * a.e.hd;
+        put4(a.e.q, qb + i0, y1);
+        put4(a.e.q, qb + i0 + half, y2);
+        return;
+      }
+      const bool isv = head >= a.e.H + a.e.Hkv;
+      const int kh = head - a.e.H - (isv ? a.e.Hkv : 0);
+      if (a.e.kv_layer) {
+        const int slot = a.e.rowslot[row], page = slot >> 6, sp = slot & 63;
+        const size_t hb = (((size_t)page * 2 + (isv ? 1 : 0)) * a.e.Hkv + kh) * 64 * a.e.hd;
+        if (!isv) {
+          put4(a.e.kv_layer, hb + (size_t)sp * a.e.hd + i0, y1);
+          put4(a.e.kv_layer, hb + (size_t)sp * a.e.hd + i0 + half, y2);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            store_elt<DT>(a.e.kv_layer, hb + (size_t)(i0 + q) * 64 + sp, y1[q]);
+            store_elt<DT>(a.e.kv_layer, hb + (size_t)(i0 + q + half) * 64 + sp, y2[q]);
+          }
+        }
+      }
+      if (a.e.kv_cap) {   // test aid: the block's k rows, then its v rows, [R][Hkv][hd]
+        const size_t cb = ((isv ? (size_t)R * a.e.Hkv : 0) + (size_t)row * a.e.Hkv + kh) * a.e.hd;
+        put4(a.e.kv_cap, cb + i0, y1);
+        put4(a.e.kv_cap, cb + i0 + half, y2);
+      }
+      return;
+    }
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2) {
+      const int tile = fg * NT + 2 * r + h2, f = 16 * tile + 4 * grp;
+      if (tile >= n_tiles) break;
+      if (EPI == EP_STORE) {
+        if (rok)
+          *reinterpret_cast<float4*>(a.e.y + (size_t)row * (16 * n_tiles) + f) =
+              make_float4(v[h2][0], v[h2][1], v[h2][2], v[h2][3]);
+      } else if (EPI == EP_RESID) {
+        float4 hv = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (rok) hv = *reinterpret_cast<const float4*>(a.e.h + (size_t)row * a.e.d + f);
+        const float4 gv = *reinterpret_cast<const float4*>(a.e.gain + f);
+        const float ho[4] = {hv.x, hv.y, hv.z, hv.w}, gn[4] = {gv.x, gv.y, gv.z, gv.w};
+        float hn[4], xv[4], ss = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          hn[q] = ho[q] + v[h2][q];
+          ss = fmaf(hn[q], hn[q], ss);
+          xv[q] = hn[q] * gn[q];
+        }
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        if (rok) {
+          *reinterpret_cast<float4*>(a.e.h + (size_t)row * a.e.d + f) = make_float4(hn[0], hn[1], hn[2], hn[3]);
+          const size_t fi = frag_index<DT>(row, f, a.e.x_S);
+          if (DT == DT_BF16)
+            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.e.xout) + fi) =
+                make_uint2(f2bf_bits(xv[0]) | (f2bf_bits(xv[1]) << 16), f2bf_bits(xv[2]) | (f2bf_bits(xv[3]) << 16));
+          else
+            *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.e.xout) + fi) = make_float4(xv[0], xv[1], xv[2], xv[3]);
+          if (grp == 0) a.e.ssqt[(size_t)row * n_tiles + tile] = ss;
+        }
+      }
+    }
+  };
+
+  // the task's chains are complete: add them in wave order, two feature tiles
+  // at a time (wave m: row tile m), and run the epilogue
+  auto reduce = [&]() {
+    int rg, fg;
+    decode(C.task, rg, fg);
+#pragma unroll
+    for (int r = 0; r < NT / 2; ++r) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) red[wv][2 * m + h2][lane] = acc[m][2 * r + h2];
+      __syncthreads();
+      if (wv < MT) {
+        f32x4 v[2];
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) {
+          v[h2] = red[0][2 * wv + h2][lane];
+#pragma unroll
+          for (int j = 1; j < W; ++j) v[h2] += red[j][2 * wv + h2][lane];
+        }
+        epilogue(rg, fg, r, v);
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+
+  // two operand buffers: the next step's fragments (of the next task, at a
+  // task's end) are requested before the current step is multiplied
+  load(xb[0], wb[0]);
+  for (;;) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      load(xb[j ^ 1], wb[j ^ 1]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[m][n] = mma<DT>(wb[j][n], xb[j][m], acc[m][n]);
+      if (++C.i == steps) {
+        reduce();
+        C.i = 0;
+        C.task += stride;
+        if (C.task >= t1) return;
+      }
+    }
+  }
+}
+
+// Row scales of the FFN-side norm from the O projection's per-tile sums of
+// h^2, in the order of ts_chunks and ts_rows: 16 tiles per chunk, then the
+// chunks.  (The gate/up kernel above forms them in its prologue.)
+__global__ __launch_bounds__(64) void tile_scale_kernel(const float* __restrict__ ssqt, int R, int d, float eps,
+                                                        float* __restrict__ rs) {
+  // four rows per workgroup, one chunk of 16 tiles per thread
+  const int ntile = d / 16, nch = d / 256;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 4), ch = threadIdx.x & 15;
+  float s = 0.f;
+  if (row < R && ch < nch) {
+    const float4* p = reinterpret_cast<const float4*>(ssqt + (size_t)row * ntile + ch * 16);
+    float4 u[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) u[q] = p[q];
+    s = u[0].x;
+    s += u[0].y;
+    s += u[0].z;
+    s += u[0].w;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+      s += u[q].x;
+      s += u[q].y;
+      s += u[q].z;
+      s += u[q].w;
+    }
+  }
+  float t = __shfl(s, threadIdx.x & ~15);
+#pragma unroll
+  for (int k = 1; k < TS_CHUNKS; ++k) {
+    const float y = __shfl(s, (threadIdx.x & ~15) + k);
+    if (k < nch) t += y;
+  }
+  if (row < R && ch == 0) rs[row] = 1.0f / sqrtf(t / (float)d + eps);
+}
+
+template <int DT, int EPI, bool NTW>
+static void launch_wide(const WideArgs& a, int mt, int nt, dim3 grid, hipStream_t st) {
+  const dim3 block(GEMM_WAVES * 64);
+  if (mt == 5 && nt == 2) hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 2, EPI, NTW>), grid, block, 0, st, a);
+  else if (mt == 5 && nt == 4) hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 4, EPI, NTW>), grid, block, 0, st, a);
+  else if (mt == 5) hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 6, EPI, NTW>), grid, block, 0, st, a);
+  else if (mt == 4) hipLaunchKernelGGL((gemm_wide_kernel<DT, 4, 6, EPI, NTW>), grid, block, 0, st, a);
+  else if (mt == 6) hipLaunchKernelGGL((gemm_wide_kernel<DT, 6, 6, EPI, NTW>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((gemm_wide_kernel<DT, 7, 4, EPI, NTW>), grid, block, 0, st, a);
+}
+
+// The projection of `a` for R rows on gemm_wide_kernel.  The tile is the one
+// with the least estimated time: rounds of 256 workgroups, each of which takes
+// in MT + NT fragments per super-step and pays about one fragment's worth of
+// fixed time.
+template <int DT, int EPI>
+static hipError_t gemm_wide(WideArgs a, int R, hipStream_t st) {
+  static const int tiles[][2] = {{5, 2}, {5, 4}, {4, 6}, {5, 6}, {6, 6}, {7, 4}};
+  a.e.R = R;
+  const int nrt = (R + 15) / 16, cols = a.e.n_items * (EPI == EP_ROPE || EPI == EP_SWIGLU ? 2 : 1);
+  int best = 0, cost = INT32_MAX;
+  for (int i = 0; i < 6; ++i) {
+    const int mt = tiles[i][0], nt = tiles[i][1];
+    const int n = ((nrt + mt - 1) / mt) * ((cols + nt - 1) / nt);
+    const int c = (n + 255) / 256 * (mt + nt + 1);
+    if (c < cost) { cost = c; best = i; }
+  }
+  const int mt = tiles[best][0], nt = tiles[best][1];
+  a.ng = (nrt + mt - 1) / mt;
+  a.ntask = a.ng * ((cols + nt - 1) / nt);
+  const dim3 grid(std::min(256, (a.ntask + 7) / 8 * 8));
+  if (a.ng == 1) launch_wide<DT, EPI, true>(a, mt, nt, grid, st);
+  else launch_wide<DT, EPI, false>(a, mt, nt, grid, st);
+  return hipGetLastError();
+}
+
+// gemm_swiglu for wide blocks; the row scales of tile sums go to `ssq` first.
+template <int DT>
+static hipError_t gemm_swiglu_wide(const uint4* wgu, const uint4* x, int F, int d, int R, void* z, float* ssq,
+                                   const float* ssqt, float eps, hipStream_t st) {
+  WideArgs a{};
+  a.e.w = wgu; a.e.x = x; a.e.S = d / Geo<DT>::KS; a.e.n_tiles = 2 * F / 16; a.e.n_items = F / 16;
+  a.e.ssq = ssq; a.e.d = d; a.e.eps = eps;
+  a.z = z; a.z_S = F / Geo<DT>::KS;
+  if (a.e.S > FK_MAX_S || F % 16 || (ssqt && (d % 256 || d > 4096))) return hipErrorInvalidValue;
+  if (ssqt) {
+    hipLaunchKernelGGL(tile_scale_kernel, dim3((R + 3) / 4), dim3(64), 0, st, ssqt, R, d, eps, ssq);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a.rs = ssq;
+  }
+  return gemm_wide<DT, EP_SWIGLU>(a, R, st);
+}
+
 // The projection of `a` (weights, activations, K = a.S super-steps, n_tiles,
 // the epilogue's operands filled in) for R rows with epilogue EPI.
 template <int DT, int EPI>
 static hipError_t gemm_ep(EpArgs a, int R, hipStream_t st) {
   if (a.S > FK_MAX_S) return hipErrorInvalidValue;
   if (EPI == EP_ROPE && (a.hd % 32 || a.n_tiles % (a.hd / 16))) return hipErrorInvalidValue;
+  if (wide_block(R, a.S, EPI)) {
+    WideArgs w{};
+    w.e = a;
+    return gemm_wide<DT, EPI>(w, R, st);
+  }
   a.R = R;
   int spw = 1;
   while (spw * GEMM_WAVES < a.S) spw *= 2;

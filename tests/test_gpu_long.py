@@ -223,3 +223,43 @@ def test_extend_commits_every_row_and_matches_oracle(ee):
     assert e.value.code == ee.EE_ECAPACITY
     assert eng.seq_state(0) == (n0 + 1, nxt)
     eng.close()
+
+
+def _models():
+    yield "f32 d256", get_shape("tiny"), 0.1
+    # an odd count of tile pairs (ffn 1120) and of vocabulary tiles (2080), 1, 3 and 8 super-steps per wave
+    yield "bf16 d256", _bf16_small(d_model=256, n_heads=4, n_kv_heads=2, head_dim=64, ffn=1120, vocab=2080), 0.05
+    yield "bf16 d768", _bf16_small(d_model=768, n_heads=6, n_kv_heads=2, ffn=1120, vocab=2080), 0.05
+    yield "bf16 d2048", _bf16_small(d_model=2048, n_heads=16, n_kv_heads=4, ffn=1120, vocab=2080), 0.03
+    yield "bf16 d4096", _bf16_small(d_model=4096, n_heads=32, n_kv_heads=8, ffn=1120, vocab=2080), 0.02
+
+
+@pytest.mark.parametrize("name,shape,std", list(_models()), ids=lambda x: x.replace(" ", "-") if isinstance(x, str) else "")
+def test_wide_blocks_equal_short_blocks_bitwise(ee, name, shape, std):
+    """The same tokens committed in one block of R rows and in blocks of at
+    most 33 rows give the same keys, values, next token and logits bit for
+    bit, at the row counts where the projections change kernel or tile: the
+    first of more than one 32-row group (34), the last of two and the first of
+    three groups (65, 66), a full and a barely started row tile (96, 97; 192,
+    193), and counts with every remainder of the row groups."""
+    w = gen_weights(shape, seed=93, gains="random", std=std)
+    prompt = zipf_tokens(shape.vocab, 70, seed=6)
+    short = ee.Engine(shape, w, max_ctx=700, k_max=32)
+    long = ee.Engine(shape, w, max_ctx=700, k_max=512)
+    short.prefill(0, prompt)
+    first = long.prefill(0, prompt)
+    short.rollback(0, 70, first)
+    for R in (34, 48, 65, 66, 96, 97, 130, 192, 193, 257, 400, 513):
+        toks = zipf_tokens(shape.vocab, R - 1, seed=R)
+        a, b = long.extend(0, toks), short.extend(0, toks)
+        assert a == b, (name, R)
+        la, lb = long.logits(), short.logits()
+        assert la.shape[0] == R
+        np.testing.assert_array_equal(la[-lb.shape[0]:], lb, err_msg=f"{name} R={R}")
+        for l in range(shape.n_layers):
+            for x, y in zip(long.read_kv(0, l), short.read_kv(0, l)):
+                np.testing.assert_array_equal(x, y, err_msg=f"{name} R={R} layer {l}")
+        long.rollback(0, 70, first)
+        short.rollback(0, 70, first)
+    short.close()
+    long.close()
