@@ -121,7 +121,8 @@ struct Step {
   int T;        // rows per sequence
   int B;        // sequences in the block
   int mode;     // 0 prefill, 1 linear verify, 2 tree verify, 3 linear top-k verify,
-                // 4 linear stochastic verify (one sequence)
+                // 4 linear stochastic verify (one sequence), 5 commit only: the
+                // rows' keys and values (no logits, no result)
   int splits;   // attention splits of the grid: the most any sequence of the
                 // block uses, ceil((n + T) / 256); 1 .. max_splits
   unsigned char* cap = nullptr;   // test aid: copies of every rounding site's

@@ -3056,6 +3056,8 @@ static hipError_t forward_t(const Model& m, const Work& w, const Step& s, Prof* 
       return e;
     }
     if (s.cap && (e = cap(l, c_q, w.q, (size_t)R * qdim * ESZ)) != hipSuccess) return e;
+    // a block that only commits rows: its keys and values are complete
+    if (s.mode == 5 && l + 1 == m.L) return hipSuccess;
     // attention
     AttnArgs aa{};
     aa.q = w.q; aa.kv_layer = kvl; aa.ptable = w.ptable; aa.pos = w.pos; aa.path = w.path;
