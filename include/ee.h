@@ -105,8 +105,10 @@ int32_t ee_create(const ee_model_config* cfg, const ee_weights* w, void* packed,
                   void* kv_pool, void* workspace, void* hip_stream, ee_ctx** out);
 int32_t ee_destroy(ee_ctx* ctx);
 
-/* Run the prompt tokens[0..n-1] of sequence `seq` (which must be empty) in
- * blocks of at most k_max+1 rows, commit all n positions to the KV cache and
+/* Run the prompt tokens[0..n-1] of sequence `seq` (which must be empty),
+ * commit all n positions to the KV cache (the last block holds the
+ * (n - 1) % (k_max + 1) + 1 last rows, the ones before it run in blocks of up
+ * to max(k_max + 1, 512) rows; results do not depend on the blocks) and
  * return the greedy token of the last row in *next_token: the first emitted
  * token of plain greedy decoding (Eq. 1, the argmax of the target's
  * distribution given the prompt), now "pending" (emitted, not yet run through
@@ -118,7 +120,7 @@ int32_t ee_prefill(ee_ctx* ctx, int32_t seq, const int32_t* tokens, int32_t n,
                    int32_t* next_token);
 
 /* Append tokens[0..n-1] to sequence `seq` without verification (n >= 0): the
- * block [pending, tokens...] is run in blocks of at most k_max+1 rows and all
+ * block [pending, tokens...] is run in blocks (as ee_prefill's) and all
  * n+1 positions are committed; *next_token = the greedy token of the last row,
  * which becomes pending.  For a model that must follow tokens chosen
  * elsewhere (a draft model catching up with the accepted output); n = 0 is

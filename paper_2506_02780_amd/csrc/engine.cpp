@@ -70,7 +70,7 @@ struct Seq {
 
 // Byte offsets of every buffer inside the three caller allocations.
 struct Layout {
-  int Tmax, Rmax, MT, G, max_splits, pages_per_seq, ptable_len, n_pages;
+  int Tmax, Rmax, Pmax, MT, G, max_splits, pages_per_seq, ptable_len, n_pages;
   // packed arena
   size_t embed, lm_head, final_gain, layers0, per_layer, l_wqkv, l_wo, l_wgu, l_wd, l_again, l_fgain,
       packed_total;
@@ -128,8 +128,8 @@ bool valid_cfg(const ee_model_config* c, std::string* why) {
 }
 
 // Columns of the largest GEMM slice-partial array of a row: max over the
-// projections of K slices x output features.
-size_t partial_cols(const ee_model_config& g) {
+// projections (and the LM head) of K slices x output features.
+size_t partial_cols(const ee_model_config& g, bool lm_head = true) {
   const int dt = g.dtype == EE_BF16 ? ee::DT_BF16 : ee::DT_F32;
   const size_t d = g.d_model, qd = (size_t)g.n_heads * g.head_dim, F = g.ffn;
   const size_t qkvN = qd + 2 * (size_t)g.n_kv_heads * g.head_dim;
@@ -138,8 +138,24 @@ size_t partial_cols(const ee_model_config& g) {
   mx = std::max(mx, (size_t)ee::gemm_slices_for((int)qd, dt) * d);
   mx = std::max(mx, (size_t)ee::gemm_slices_for((int)d, dt) * 2 * F);
   mx = std::max(mx, (size_t)ee::gemm_slices_for((int)F, dt) * d);
-  mx = std::max(mx, (size_t)ee::gemm_slices_for((int)d, dt) * (size_t)g.vocab);
+  if (lm_head) mx = std::max(mx, (size_t)ee::gemm_slices_for((int)d, dt) * (size_t)g.vocab);
   return mx;
+}
+
+// Rows of the commit-only blocks of prompts and extensions: up to 512 whatever
+// k_max is, since a block streams every weight once for all of its rows (1B,
+// 1000 tokens, k_max 64: 14.25 ms in 65-row blocks, 5.0 ms in blocks of 512,
+// 463 and 25 rows), halved until the block's attention states, GEMM
+// partials and query columns stay within the bounds that valid_cfg sets for
+// verify blocks; at least k_max + 1.
+int prompt_rows(const ee_model_config& g) {
+  const int Tmax = g.k_max + 1;
+  const size_t splits = (g.max_ctx + SPLIT - 1) / SPLIT + 1;
+  for (int p = std::min(512, (g.max_ctx + 15) / 16 * 16); p > Tmax; p = p / 2 / 16 * 16)
+    if (splits * g.n_heads * p * (g.head_dim + 2) * 4 < (size_t(1) << 31) &&
+        partial_cols(g, false) * p * 4 < (size_t(1) << 31) && g.n_heads / g.n_kv_heads * p <= 64 * 16 * 16)
+      return p;
+  return Tmax;
 }
 
 Layout make_layout(const ee_model_config* c) {
@@ -150,7 +166,9 @@ Layout make_layout(const ee_model_config* c) {
   const size_t F = c->ffn, V = c->vocab;
   L.Tmax = c->k_max + 1;
   L.Rmax = L.Tmax * c->max_seqs;   // a block holds up to max_seqs sequences
-  L.MT = (L.Rmax + 15) / 16;
+  L.Pmax = prompt_rows(*c);
+  const size_t Rall = std::max(L.Rmax, L.Pmax);   // rows of any block
+  L.MT = (Rall + 15) / 16;
   L.G = c->n_heads / c->n_kv_heads;
   L.max_splits = (c->max_ctx + SPLIT - 1) / SPLIT + 1;
   L.pages_per_seq = (c->max_ctx + PAGE - 1) / PAGE;
@@ -176,16 +194,16 @@ Layout make_layout(const ee_model_config* c) {
   const size_t Tpad = (size_t)L.MT * 16;
   const size_t xcols = std::max(d, H * hd);
   o = 0;
-  L.h = o; o += up(L.Rmax * d * 4);
-  L.ssq = o; o += up((size_t)L.Rmax * 8 * 4);
+  L.h = o; o += up(Rall * d * 4);
+  L.ssq = o; o += up(Rall * 8 * 4);
   L.xbuf = o; o += up(Tpad * xcols * esz);
   L.x2buf = o; o += up(Tpad * d * esz);
-  L.ssqt = o; o += up((size_t)L.Rmax * (d / 16) * 4);
+  L.ssqt = o; o += up(Rall * (d / 16) * 4);
   L.zbuf = o; o += up(Tpad * F * esz);
-  L.q = o; o += up(L.Rmax * H * hd * esz);
-  L.part = o; o += up((size_t)L.max_splits * Hkv * L.Rmax * L.G * (hd + 2) * 4);
-  // split-K partials of the largest GEMM: [slices][Rmax][N]
-  L.gpart = o; o += up(partial_cols(*c) * L.Rmax * 4);
+  L.q = o; o += up(Rall * H * hd * esz);
+  L.part = o; o += up((size_t)L.max_splits * Hkv * Rall * L.G * (hd + 2) * 4);
+  // split-K partials of the largest GEMM: [slices][rows][N]
+  L.gpart = o; o += up(std::max(partial_cols(*c) * L.Rmax, partial_cols(*c, false) * Rall) * 4);
   L.logits = o; o += up(L.Rmax * V * 4);
   L.amax = o; o += up(L.Rmax * ((V + 2047) / 2048) * 8 * 8);
   L.greedy = o; o += up(L.Rmax * 4);
@@ -195,10 +213,10 @@ Layout make_layout(const ee_model_config* c) {
   L.result = o; o += up((size_t)c->max_seqs * (2 + c->k_max) * 4);
   // staging block: read from its pinned host mirror by the block's first kernel
   size_t so = 0;
-  L.s_tok = so; so += L.Rmax * 4;
-  L.s_pos = so; so += L.Rmax * 4;
-  L.s_prow = so; so += L.Rmax * 4;
-  L.s_slot = so; so += L.Rmax * 4;
+  L.s_tok = so; so += Rall * 4;
+  L.s_pos = so; so += Rall * 4;
+  L.s_prow = so; so += Rall * 4;
+  L.s_slot = so; so += Rall * 4;
   L.s_path = so; so += L.Rmax * 64;
   so = (so + 15) & ~(size_t)15;   // 16-byte loads of page numbers
   L.s_ptable = so; so += (size_t)c->max_seqs * L.ptable_len * 4;
@@ -476,8 +494,11 @@ int run_block(ee_ctx* c, Seq* const* seqs, int B, int T, int mode, int top_k = 0
   step.cap = c->cap;
   ee::Prof* prof = c->prof.mask ? &c->prof : nullptr;
   // events recorded by graph nodes cannot be timed, and captures are copies
-  // of a test aid: profiled or captured blocks run eagerly
-  const ee_ctx::Captured* cg = (prof || c->cap || scratch_work) ? nullptr : block_graph(c, step, nullptr);
+  // of a test aid: profiled or captured blocks run eagerly; so do commit-only
+  // blocks, whose row counts follow the prompt's length (a graph per length
+  // would be captured again and again) and whose launches run ahead of the GPU
+  const bool eager = prof || c->cap || scratch_work || mode == 5;
+  const ee_ctx::Captured* cg = eager ? nullptr : block_graph(c, step, nullptr);
   if (cg) {
     HIP_TRY(c, hipGraphLaunch(cg->exec, c->st));
     c->prof.used = cg->prof_pairs;
@@ -544,13 +565,15 @@ void stage_draft(ee_ctx* c, int b, int T, const Seq& s, const int32_t* draft, co
   }
 }
 
-// Run rows[0..n) at positions len.. in blocks of at most k_max + 1 rows and
-// commit all of them (every row's K/V kept); *last = the greedy token of the
-// final row.  Only the last block's logits can be read, so the blocks before
-// it stop once their keys and values are in the cache: no final layer past its
-// QKV projection, no LM head (312 us per 513-row block at the 7B width).  (A
-// rounding-site capture records whole blocks.)  On failure the sequence is
-// left as it was.
+// Run rows[0..n) at positions len.. and commit all of them (every row's K/V
+// kept); *last = the greedy token of the final row.  The last block has the
+// rows left over by whole blocks of k_max + 1 (at least one): only its logits
+// can be read, so the rows before it run in commit-only blocks of up to Pmax
+// rows, which stop once their keys and values are in the cache: no final layer
+// past its QKV projection, no LM head (312 us per 513-row block at the 7B
+// width).  A row's arithmetic does not depend on its block.  (A rounding-site
+// capture records whole blocks of at most k_max + 1 rows.)  On failure the
+// sequence is left as it was.
 int commit_rows(ee_ctx* c, Seq& s, const int32_t* rows, int n, int* last) {
   const Layout& L = c->lay;
   int added;
@@ -558,16 +581,18 @@ int commit_rows(ee_ctx* c, Seq& s, const int32_t* rows, int n, int* last) {
   int* tok = reinterpret_cast<int*>(c->h_stage + L.s_tok);
   int* pos = reinterpret_cast<int*>(c->h_stage + L.s_pos);
   int* prow = reinterpret_cast<int*>(c->h_stage + L.s_prow);
-  const int len0 = s.len;
-  for (int off = 0; off < n; off += L.Tmax) {
-    const int T = std::min(L.Tmax, n - off);
+  const int len0 = s.len, lead = (n - 1) / L.Tmax * L.Tmax;   // rows before the last block
+  const int most = c->cap ? L.Tmax : std::max(L.Tmax, L.Pmax);
+  int T;
+  for (int off = 0; off < n; off += T) {
+    const bool final = off >= lead;
+    T = final ? n - off : std::min(most, lead - off);
     for (int r = 0; r < T; ++r) {
       tok[r] = rows[off + r];
       pos[r] = s.len + r;
       prow[r] = r - 1;
     }
     Seq* one = &s;
-    const bool final = off + T == n;
     const int rc = run_block(c, &one, 1, T, final || c->cap ? 0 : 5);
     if (rc) {
       s.len = len0;

@@ -263,3 +263,49 @@ def test_wide_blocks_equal_short_blocks_bitwise(ee, name, shape, std):
         short.rollback(0, 70, first)
     short.close()
     long.close()
+
+
+@pytest.mark.parametrize("k_max", [0, 8, 64])
+def test_prompt_blocks_beyond_k_max_equal_draft_sized_blocks_bitwise(ee, k_max):
+    """A prompt's rows before its last block run in blocks of up to 512 rows
+    whatever k_max is: keys, values, next token and the last block's logits
+    equal those of an engine fed the same tokens k_max + 1 rows at a time, for
+    prompts that end on, before and after a block of either size, and for an
+    extension in the middle of a sequence."""
+    shape = _bf16_small()
+    w = gen_weights(shape, seed=94, gains="random", std=0.05)
+    toks = zipf_tokens(shape.vocab, 1150, seed=8)
+    eng = ee.Engine(shape, w, max_ctx=1200, k_max=k_max)
+    ref = ee.Engine(shape, w, max_ctx=1200, k_max=k_max)
+    T = k_max + 1
+
+    def same(n):
+        la, lb = eng.logits(), ref.logits()
+        np.testing.assert_array_equal(la, lb)
+        assert la.shape[0] == (n - 1) % T + 1
+        for l in range(shape.n_layers):
+            for x, y in zip(eng.read_kv(0, l), ref.read_kv(0, l)):
+                np.testing.assert_array_equal(x, y)
+
+    for n in ((T, 37, 130) if k_max == 0 else (T, T + 1, 2 * T, 512, 513, 1100)):
+        a = eng.prefill(0, toks[:n])
+        # one block per call: the first prefills, the others follow its tokens
+        b = ref.prefill(0, toks[:min(T, n)])
+        for off in range(T, n, T):
+            ref.rollback(0, off, int(toks[off]))
+            b = ref.extend(0, toks[off + 1:min(off + T, n)])
+        assert a == b and eng.seq_state(0)[0] == ref.seq_state(0)[0] == n
+        same(n)
+        more = zipf_tokens(shape.vocab, min(40, 1150 - n), seed=n)
+        a = eng.extend(0, more)
+        ref.rollback(0, n, b)
+        rows = np.concatenate([[b], more])
+        for off in range(0, len(rows), T):
+            ref.rollback(0, n + off, int(rows[off]))
+            c = ref.extend(0, rows[off + 1:off + T])
+        assert a == c
+        same(len(rows))
+        eng.rollback(0, 0, -1)
+        ref.rollback(0, 0, -1)
+    eng.close()
+    ref.close()
