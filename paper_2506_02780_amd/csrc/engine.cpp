@@ -75,7 +75,7 @@ struct Layout {
   size_t embed, lm_head, final_gain, layers0, per_layer, l_wqkv, l_wo, l_wgu, l_wd, l_again, l_fgain,
       packed_total;
   // workspace
-  size_t h, ssq, xbuf, x2buf, ssqt, zbuf, q, part, gpart, logits, amax, greedy, verdict, rowstat, ebuf, result, stage, rope, ws_total;
+  size_t h, ssq, xbuf, x2buf, ssqt, zbuf, q, part, gpart, logits, amax, greedy, verdict, rowstat, result, stage, rope, ws_total;
   // staging sub-offsets (relative to `stage`)
   size_t s_tok, s_pos, s_prow, s_slot, s_path, s_ptable, s_info, s_eps, s_unif, s_sparam, stage_bytes;
   size_t kv_layer, kv_total;
@@ -209,7 +209,6 @@ Layout make_layout(const ee_model_config* c) {
   L.greedy = o; o += up(L.Rmax * 4);
   L.verdict = o; o += up(L.Rmax * 4);
   L.rowstat = o; o += up((size_t)L.Rmax * 2 * 8);
-  L.ebuf = o; o += up((size_t)L.Rmax * V * 8);
   L.result = o; o += up((size_t)c->max_seqs * (2 + c->k_max) * 4);
   // staging block: read from its pinned host mirror by the block's first kernel
   size_t so = 0;
@@ -313,7 +312,6 @@ void bind_work(ee_ctx* c) {
   w.greedy = reinterpret_cast<int*>(ws + L.greedy);
   w.verdict = reinterpret_cast<int*>(ws + L.verdict);
   w.rowstat = reinterpret_cast<double*>(ws + L.rowstat);
-  w.ebuf = reinterpret_cast<double*>(ws + L.ebuf);
   w.result = reinterpret_cast<int*>(ws + L.result);
   unsigned char* sb = ws + L.stage;
   w.path = sb + L.s_path;

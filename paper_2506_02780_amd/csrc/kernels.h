@@ -73,11 +73,11 @@ struct Work {
   float* attn_part;         // [splits][Hkv][Rmax*G][hd + 2]
   float* part;              // GEMM slice partials [SK][R][N]
   float* logits;            // [Rmax, V]
-  unsigned long long* amax; // [Rmax, ceil(V/2048), 8] chunk maxima (top-8 in mode 3)
+  unsigned long long* amax; // [Rmax, ceil(V/2048), 8] chunk maxima (top-8 in mode 3; in mode 4
+                            // then the chunk sums of the exponentials)
   int* greedy;              // [Rmax]
-  int* verdict;             // [Rmax] modes 3, 4: tau | draft-accepted << 8
+  int* verdict;             // [Rmax] mode 3: tau | draft-accepted << 8
   double* rowstat;          // [Rmax][2] mode 4: row maximum and sum of exp((l - max) / temperature)
-  double* ebuf;             // [Rmax][V] mode 4: exp((l - max) / temperature) of every logit
   int* result;              // [max_seqs][rec]: accept_len, next, accepted rows (or thresholds)
   // staged per call (host -> device)
   int* tok;                 // [Rmax]

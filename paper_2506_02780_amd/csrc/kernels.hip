@@ -2612,183 +2612,256 @@ __global__ __launch_bounds__(64) void topk_select_kernel(const unsigned long lon
   }
 }
 
-// Stochastic verification (Eq. 4), step 1, one workgroup per row: the row's
-// maximum logit M (from the chunk maxima), e_v = exp((l_v - M) / temp) (kept
-// in ebuf[t] for the draw that may follow at this row) and S = sum_v e_v, in
-// float64 with a fixed summation order; draft row t (t + 1 < T) accepts token
-// d = tok[t + 1] when eps_t * q_t[d] < p_t[d] = e_d / S, with q_t[d] from the
-// draft distribution (1 when none is given: a greedy draft).  verdict[t] bit
-// 8 = accepted; greedy[t] = the row's argmax; rowstat[t] = (M, S).
+// Stochastic verification (Eq. 4).  With M the row's maximum logit (from the
+// chunk maxima) and e_v = exp((l_v - M) / temp), in float64:
+//   sample_sums_kernel    S = sum e_v per 2048-column chunk, a workgroup each;
+//   sample_accept_kernel  S of every row (chunks in order); draft row t (t + 1
+//                         < T) accepts d = tok[t + 1] when eps_t q_t[d] <
+//                         e_d / S (q_t[d] = 1 for a greedy draft); the first
+//                         failing row is a;
+//   resample_sums_kernel  the weights of row a summed per 64-token group;
+//   resample_kernel       the draw.
+// Everything is bound by float64 exponentials and round trips, so the row sums
+// spread over V / 2048 workgroups per row and the group sums over V / 1024 (one
+// workgroup per row and a single one for the draw took 47 + 54 us at 25 rows
+// of 32256 tokens; the four kernels take 5 + 5 + 5.5 + 8), and the exponentials
+// of row a are formed again rather than kept for every row (8 bytes per logit).
 struct SampleParams {
   unsigned long long q;   // device address of the draft distribution [K][V] fp32, or 0
   float temperature;
   int residual;
 };
 constexpr int SAMPLE_MAX_GROUPS = 4096;   // 64-token groups: vocabularies up to 262144 tokens
+constexpr int RSUM_GROUPS = 16;           // groups per workgroup of resample_sums_kernel
 
-__device__ __forceinline__ double sample_weight(const double* e, const float* q, int d, int v, double S, bool resid) {
-  if (!resid) return e[v];
-  const double p = e[v] / S;
+__device__ __forceinline__ double sample_exp(float l, double M, double it) { return exp(((double)l - M) * it); }
+
+// Weight of token v of the row drawn from: e_v, or with `resid` the residual
+// max(0, p_v - q_v) (q null: one-hot at d).
+__device__ __forceinline__ double sample_weight(double e, const float* q, int d, int v, double S, bool resid) {
+  if (!resid) return e;
+  const double p = e / S;
   const double qv = q ? (double)q[v] : (v == d ? 1.0 : 0.0);
   return p > qv ? p - qv : 0.0;
 }
 
-__global__ __launch_bounds__(256) void sample_stats_kernel(const float* __restrict__ logits,
-                                                           const unsigned long long* __restrict__ amax, int nchunk,
-                                                           int V, const int* __restrict__ tok, int T,
-                                                           const float* __restrict__ eps,
-                                                           const unsigned char* __restrict__ sparam,
-                                                           double* __restrict__ rowstat, double* __restrict__ ebuf,
-                                                           int* __restrict__ greedy, int* __restrict__ verdict) {
-  __shared__ double sh[256];
-  __shared__ unsigned long long shk[256];
-  const int t = blockIdx.x, tid = threadIdx.x;
+__global__ __launch_bounds__(256) void sample_sums_kernel(const float* __restrict__ logits,
+                                                          const unsigned long long* __restrict__ amax, int nchunk,
+                                                          int V, const unsigned char* __restrict__ sparam,
+                                                          double* __restrict__ csum) {
+  __shared__ double sh[4];
+  const int t = blockIdx.y, lane = threadIdx.x & 63;
   const SampleParams sp = *reinterpret_cast<const SampleParams*>(sparam);
-  unsigned long long best = 0;
-  for (int i = tid; i < nchunk; i += 256) best = amax[(size_t)t * nchunk + i] > best ? amax[(size_t)t * nchunk + i] : best;
-  shk[tid] = best;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w && shk[tid + w] > shk[tid]) shk[tid] = shk[tid + w];
-    __syncthreads();
+  const int col = (blockIdx.x * 256 + threadIdx.x) * 8;
+  float l[8];
+  if (col < V) {   // V is a multiple of 16: a thread's 8 columns are all in range or all out
+    const float4* lp = reinterpret_cast<const float4*>(logits + (size_t)t * V + col);
+    const float4 a = lp[0], b = lp[1];
+    l[0] = a.x; l[1] = a.y; l[2] = a.z; l[3] = a.w;
+    l[4] = b.x; l[5] = b.y; l[6] = b.z; l[7] = b.w;
   }
-  const unsigned long long key = shk[0];
-  const double M = (double)key_value(key), it = 1.0 / (double)sp.temperature;
-  const float* row = logits + (size_t)t * V;
-  double* e = ebuf + (size_t)t * V;
+  unsigned long long best = 0;   // every wave finds the row's maximum itself
+  for (int i = lane; i < nchunk; i += 64) best = max(best, amax[(size_t)t * nchunk + i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) best = max(best, (unsigned long long)__shfl_xor(best, o));
+  const double M = (double)key_value(best), it = 1.0 / (double)sp.temperature;
   double acc = 0.0;
-  for (int v = tid; v < V; v += 256) {
-    const double ev = exp(((double)row[v] - M) * it);
-    e[v] = ev;
-    acc += ev;
+  if (col < V) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc += sample_exp(l[e], M, it);
   }
-  sh[tid] = acc;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  if (lane == 0) sh[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) sh[tid] += sh[tid + w];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    const double S = sh[0];
+  if (threadIdx.x == 0) csum[(size_t)t * nchunk + blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
+}
+
+// result[0] = a, result[1] = row a's argmax (replaced by the draw), result[2..2+a)
+// = the accepted rows; rowstat[t] = (M, S).  One workgroup, one thread per row.
+__global__ __launch_bounds__(256) void sample_accept_kernel(const float* __restrict__ logits,
+                                                            const unsigned long long* __restrict__ amax,
+                                                            const double* __restrict__ csum, int nchunk, int V,
+                                                            const int* __restrict__ tok, int T,
+                                                            const float* __restrict__ eps,
+                                                            const unsigned char* __restrict__ sparam,
+                                                            double* __restrict__ rowstat, int* __restrict__ greedy,
+                                                            int* __restrict__ result) {
+  __shared__ int fail;
+  const SampleParams sp = *reinterpret_cast<const SampleParams*>(sparam);
+  const double it = 1.0 / (double)sp.temperature;
+  const int K = T - 1;
+  if (threadIdx.x == 0) fail = K;
+  __syncthreads();
+  for (int t = threadIdx.x; t < T; t += 256) {
+    unsigned long long best = 0;
+    double S = 0.0;
+    for (int i = 0; i < nchunk; ++i) {
+      best = max(best, amax[(size_t)t * nchunk + i]);
+      S += csum[(size_t)t * nchunk + i];
+    }
+    const double M = (double)key_value(best);
     rowstat[2 * t] = M;
     rowstat[2 * t + 1] = S;
-    greedy[t] = key_index(key);
-    int ok = 0;
-    if (t + 1 < T) {
+    greedy[t] = key_index(best);
+    if (t < K) {
       const int d = tok[t + 1];
-      const double pd = exp(((double)row[d] - M) * it) / S;
+      const double pd = sample_exp(logits[(size_t)t * V + d], M, it) / S;
       const double qd = sp.q ? (double)reinterpret_cast<const float*>(sp.q)[(size_t)t * V + d] : 1.0;
-      ok = (double)eps[t] * qd < pd ? 1 : 0;
+      if (!((double)eps[t] * qd < pd)) atomicMin(&fail, t);
     }
-    verdict[t] = ok << 8;
+  }
+  __syncthreads();
+  const int a = fail;
+  if (threadIdx.x == 0) result[0] = a;
+  for (int i = threadIdx.x; i < a; i += 256) result[2 + i] = i + 1;
+}
+
+// What row a = result[0] is drawn from: a rejected draft row (a < K) with
+// `residual` from the residual of its draft distribution, else from e.
+struct Drawn {
+  int a, d;
+  bool resid;
+  double M, S, it;
+  const float* q;
+  const float* row;
+};
+__device__ __forceinline__ Drawn drawn_row(const float* logits, int V, const int* tok, int T,
+                                           const unsigned char* sparam, const double* rowstat, const int* result) {
+  const SampleParams sp = *reinterpret_cast<const SampleParams*>(sparam);
+  Drawn r;
+  r.a = result[0];
+  const bool draft_row = r.a < T - 1;
+  r.d = draft_row ? tok[r.a + 1] : -1;
+  r.resid = draft_row && sp.residual;
+  r.M = rowstat[2 * r.a];
+  r.S = rowstat[2 * r.a + 1];
+  r.it = 1.0 / (double)sp.temperature;
+  r.q = (draft_row && sp.q) ? reinterpret_cast<const float*>(sp.q) + (size_t)r.a * V : nullptr;
+  r.row = logits + (size_t)r.a * V;
+  return r;
+}
+
+// gsum[g] = sum of e over the 64 tokens of group g, gsum[ng + g] = sum of the
+// residual weights (one token per lane, four groups per wave).
+__global__ __launch_bounds__(256) void resample_sums_kernel(const float* __restrict__ logits, int V,
+                                                            const int* __restrict__ tok, int T,
+                                                            const unsigned char* __restrict__ sparam,
+                                                            const double* __restrict__ rowstat,
+                                                            const int* __restrict__ result, double* __restrict__ gsum) {
+  constexpr int GPW = RSUM_GROUPS / 4;
+  const Drawn r = drawn_row(logits, V, tok, T, sparam, rowstat, result);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, ng = (V + 63) / 64;
+  double e[GPW], w[GPW];
+#pragma unroll
+  for (int i = 0; i < GPW; ++i) {
+    const int v = (blockIdx.x * RSUM_GROUPS + wv * GPW + i) * 64 + lane;
+    e[i] = v < V ? sample_exp(r.row[v], r.M, r.it) : 0.0;
+    w[i] = v < V && r.resid ? sample_weight(e[i], r.q, r.d, v, r.S, true) : 0.0;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int i = 0; i < GPW; ++i) {
+      e[i] += __shfl_xor(e[i], o);
+      w[i] += __shfl_xor(w[i], o);
+    }
+#pragma unroll
+  for (int i = 0; i < GPW; ++i) {
+    const int g = blockIdx.x * RSUM_GROUPS + wv * GPW + i;
+    if (lane == 0 && g < ng) {
+      gsum[g] = e[i];
+      gsum[ng + g] = w[i];
+    }
   }
 }
 
-// Stochastic verification, step 2 (after the acceptance scan), one workgroup:
-// row a = result[0] draws the next token by inverse CDF with u = unif[a] over
-// w_v = max(0, p_v - q_v) (a rejected draft row with `residual`; p instead
-// when the residual vanishes) or over e_v, proportional to p (the bonus row,
-// or no residual): the smallest v whose cumulative weight in token order
-// exceeds u times the total.  The vocabulary is cut into 64-token groups;
-// group sums (tiles of 64 groups transposed through LDS, each summed in token
-// order), runs of groups per thread, run offsets in thread order, then an
-// inclusive scan over the chosen group's tokens.  float64; rounding that
-// leaves the target past every sum picks the last token of non-zero weight.
-__global__ __launch_bounds__(256) void resample_kernel(const double* __restrict__ ebuf, int V, const int* __restrict__ tok,
-                                                       int T, const float* __restrict__ unif,
+// The next token by inverse CDF with u = unif[a]: the smallest token whose
+// cumulative weight in token order exceeds u times the total (the residual
+// weights, or e where none is left: p == q).  Runs of groups per thread, run
+// offsets by a scan in thread order, the run's groups in order, then an
+// inclusive scan over the chosen group's tokens.  Rounding that leaves the
+// target past every sum picks the last token of non-zero weight.
+__global__ __launch_bounds__(256) void resample_kernel(const float* __restrict__ logits, int V,
+                                                       const int* __restrict__ tok, int T,
+                                                       const float* __restrict__ unif,
                                                        const unsigned char* __restrict__ sparam,
-                                                       const double* __restrict__ rowstat, int* __restrict__ result) {
-  __shared__ double tile[64][65];
+                                                       const double* __restrict__ rowstat,
+                                                       const double* __restrict__ gsum, int* __restrict__ result) {
   __shared__ double gs[SAMPLE_MAX_GROUPS];
-  __shared__ double run_s[256], run_o[257];
-  __shared__ int sel[2];
+  __shared__ double wsum[4];
+  __shared__ int pick, last;
+  __shared__ int sel;
   __shared__ double sel_off;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const SampleParams sp = *reinterpret_cast<const SampleParams*>(sparam);
-  const int a = result[0];
-  const int K = T - 1;
-  const double S = rowstat[2 * a + 1];
-  const double* e = ebuf + (size_t)a * V;
-  const bool draft_row = a < K;
-  const int d = draft_row ? tok[a + 1] : -1;
-  const float* q = (draft_row && sp.q) ? reinterpret_cast<const float*>(sp.q) + (size_t)a * V : nullptr;
-  bool resid = draft_row && sp.residual;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const Drawn r = drawn_row(logits, V, tok, T, sparam, rowstat, result);
   const int ng = (V + 63) / 64, per = (ng + 255) / 256;
   const int r0 = min(ng, tid * per), r1 = min(ng, r0 + per);
+  bool resid = r.resid;
+  double run = 0.0, off = 0.0, total = 0.0;
   for (int pass = 0; pass < 2; ++pass) {
-    for (int base = 0; base < ng; base += 64) {
-      for (int k = tid; k < 64 * 64; k += 256) {
-        const int v = base * 64 + k;
-        tile[k >> 6][k & 63] = v < V ? sample_weight(e, q, d, v, S, resid) : 0.0;
-      }
-      __syncthreads();
-      if (tid < 64 && base + tid < ng) {
-        double sum = 0.0;
-        for (int j = 0; j < 64; ++j) sum += tile[tid][j];
-        gs[base + tid] = sum;
-      }
-      __syncthreads();
-    }
-    double run = 0.0;
-    for (int g = r0; g < r1; ++g) run += gs[g];
-    run_s[tid] = run;
-    __syncthreads();
-    if (tid == 0) {
-      double o = 0.0;
-      for (int i = 0; i < 256; ++i) {
-        run_o[i] = o;
-        o += run_s[i];
-      }
-      run_o[256] = o;
-    }
-    __syncthreads();
-    if (!(resid && !(run_o[256] > 0.0))) break;
-    resid = false;   // p == q: nothing to correct, draw from p
-    __syncthreads();
-  }
-  const double target = (double)unif[a] * run_o[256];
-  if (tid == 0) {
-    sel[0] = -1;
-    sel[1] = -1;
-  }
-  __syncthreads();
-  // the run, then the group, holding the target; else the last group of non-zero weight
-  if (r0 < r1 && target >= run_o[tid] && target < run_o[tid] + run_s[tid]) {
-    double c = run_o[tid];
+    const double* src = gsum + (resid ? ng : 0);
+    run = 0.0;
     for (int g = r0; g < r1; ++g) {
-      if (gs[g] > 0.0 && target < c + gs[g]) {
-        sel[0] = g;
-        sel_off = c;
-        break;
-      }
-      c += gs[g];
+      gs[g] = src[g];
+      run += gs[g];
     }
-  }
-  __syncthreads();
-  if (tid == 0 && sel[0] < 0) {
-    double c = 0.0;
-    for (int g = 0; g < ng; ++g) {
-      if (gs[g] > 0.0) {
-        sel[0] = g;
-        sel_off = c;
-      }
-      c += gs[g];
-    }
-    if (sel[0] < 0) sel[0] = 0;
-  }
-  __syncthreads();
-  if (tid < 64) {
-    const int g = sel[0];
-    const int v = g * 64 + lane;
-    const double wv = v < V ? sample_weight(e, q, d, v, S, resid) : 0.0;
-    double incl = wv;   // inclusive scan over the group in token order
+    // inclusive scan over the threads
+    double incl = run;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const double y = __shfl_up(incl, o);
       if (lane >= o) incl += y;
     }
-    const unsigned long long over = __ballot(wv > 0.0 && sel_off + incl > target);
-    const unsigned long long pos = __ballot(wv > 0.0);
+    if (lane == 63) wsum[wv] = incl;
+    __syncthreads();
+    double before = 0.0;
+    for (int i = 0; i < wv; ++i) before += wsum[i];
+    total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    off = before + (incl - run);
+    if (!(resid && !(total > 0.0))) break;   // (uniform)
+    resid = false;   // p == q: nothing to correct, draw from p
+    __syncthreads();
+  }
+  const double target = (double)unif[r.a] * total;
+  if (tid == 0) {
+    pick = 256;
+    last = -1;
+    sel = 0;
+    sel_off = 0.0;
+  }
+  __syncthreads();
+  if (run > 0.0) {
+    if (target < off + run) atomicMin(&pick, tid);
+    atomicMax(&last, tid);
+  }
+  __syncthreads();
+  // the first run reaching past the target (else the last of non-zero weight),
+  // and in it the first group doing so (else its last of non-zero weight)
+  if (tid == (pick < 256 ? pick : last)) {
+    double c = off;
+    for (int g = r0; g < r1; ++g) {
+      if (gs[g] > 0.0) {
+        sel = g;
+        sel_off = c;
+        if (pick < 256 && target < c + gs[g]) break;
+      }
+      c += gs[g];
+    }
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const int g = sel;
+    const int v = g * 64 + lane;
+    const double wv2 = v < V ? sample_weight(sample_exp(r.row[v], r.M, r.it), r.q, r.d, v, r.S, resid) : 0.0;
+    double incl = wv2;   // inclusive scan over the group in token order
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const double y = __shfl_up(incl, o);
+      if (lane >= o) incl += y;
+    }
+    const unsigned long long over = __ballot(wv2 > 0.0 && sel_off + incl > target);
+    const unsigned long long pos = __ballot(wv2 > 0.0);
     int chosen;
     if (over) chosen = g * 64 + (__ffsll((long long)over) - 1);
     else chosen = pos ? g * 64 + (63 - __clzll((long long)pos)) : g * 64;
@@ -2819,9 +2892,9 @@ __global__ __launch_bounds__(64) void accept_kernel(const int* __restrict__ tok,
     }
     return;
   }
-  if (mode == 1 || mode == 3 || mode == 4) {
+  if (mode == 1 || mode == 3) {
     // draft d_{i+1} (row i+1) is checked against row i: its greedy token
-    // (mode 1) or its verdict (mode 3: top-k, mode 4: stochastic); the first
+    // (mode 1) or its verdict (mode 3: top-k); the first
     // failing row, found 64 rows at a time, is a.  Mode 3 also records every
     // row's threshold.
     int a = K;
@@ -2831,8 +2904,6 @@ __global__ __launch_bounds__(64) void accept_kernel(const int* __restrict__ tok,
       if (i < K) {
         if (mode == 1) {
           fails = tok[i + 1] != greedy[i];
-        } else if (mode == 4) {
-          fails = !((verdict[i] >> 8) & 1);
         } else {
           const int vd = verdict[i];
           fails = !((vd >> 8) & 1);
@@ -3202,9 +3273,9 @@ static hipError_t forward_t(const Model& m, const Work& w, const Step& s, Prof* 
     if (topk)
       hipLaunchKernelGGL(topk_select_kernel, dim3(R), dim3(64), 0, st, w.amax, nchunk, w.tok, w.info, s.T,
                          w.greedy, w.verdict);
-    else if (s.mode == 4)
-      hipLaunchKernelGGL(sample_stats_kernel, dim3(R), dim3(256), 0, st, w.logits, w.amax, nchunk, m.V, w.tok, s.T,
-                         w.eps, w.sparam, w.rowstat, w.ebuf, w.greedy, w.verdict);
+    else if (s.mode == 4)   // (chunk sums behind the chunk maxima, whose buffer has room for 8 keys per chunk)
+      hipLaunchKernelGGL(sample_sums_kernel, dim3(nchunk, R), dim3(256), 0, st, w.logits, w.amax, nchunk, m.V,
+                         w.sparam, reinterpret_cast<double*>(w.amax + (size_t)R * nchunk));
     else
       hipLaunchKernelGGL(argmax_kernel, dim3(R), dim3(256), 0, st, w.amax, nchunk, w.greedy);
     return last();
@@ -3253,11 +3324,20 @@ hipError_t run_forward(const Model& m, const Work& w, const Step& s, Prof* prof,
 
 hipError_t run_accept(const Model& m, const Work& w, const Step& s, Prof* prof, hipStream_t st) {
   return timed(prof, PC_ACCEPT, st, [&] {
+    if (s.mode == 4) {   // one sequence: acceptance, then the draw at the accepted length
+      const int nchunk = (m.V + 2047) / 2048, ng = (m.V + 63) / 64;
+      double* csum = reinterpret_cast<double*>(w.amax + (size_t)s.T * nchunk);
+      double* gsum = reinterpret_cast<double*>(w.part);   // (the GEMM partials are consumed: at least 4 V bytes)
+      hipLaunchKernelGGL(sample_accept_kernel, dim3(1), dim3(256), 0, st, w.logits, w.amax, csum, nchunk, m.V, w.tok,
+                         s.T, w.eps, w.sparam, w.rowstat, w.greedy, w.result);
+      hipLaunchKernelGGL(resample_sums_kernel, dim3((ng + RSUM_GROUPS - 1) / RSUM_GROUPS), dim3(256), 0, st, w.logits,
+                         m.V, w.tok, s.T, w.sparam, w.rowstat, w.result, gsum);
+      hipLaunchKernelGGL(resample_kernel, dim3(1), dim3(256), 0, st, w.logits, m.V, w.tok, s.T, w.unif, w.sparam,
+                         w.rowstat, gsum, w.result);
+      return hipGetLastError();
+    }
     hipLaunchKernelGGL(accept_kernel, dim3(s.B), dim3(64), 0, st, w.tok, w.prow, w.greedy, w.verdict, s.T,
                        s.mode, w.result, w.rec);
-    if (s.mode == 4)   // one sequence: draw the next token at the accepted length
-      hipLaunchKernelGGL(resample_kernel, dim3(1), dim3(256), 0, st, w.ebuf, m.V, w.tok, s.T, w.unif, w.sparam,
-                         w.rowstat, w.result);
     return hipGetLastError();
   });
 }

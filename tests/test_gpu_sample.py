@@ -127,3 +127,46 @@ def test_greedy_draft_at_low_temperature_is_greedy_verification(ee):
     assert e.value.code == ee.EE_EINVAL
     assert eng.seq_state(0) == (n0, p0)
     eng.close()
+
+
+@pytest.mark.parametrize("vocab", [48, 1040, 16496, 66064])
+def test_sampling_over_vocabularies_equals_the_rule_on_the_same_logits(ee, vocab):
+    """The acceptance and the draw against Eq. 4 in float64 on the GPU's own
+    logits (no logit error left), for vocabularies smaller than a 64-token
+    group, ending inside a group and inside a 2048-column chunk, and of more
+    groups than threads; greedy drafts and draft distributions, one equal to
+    the target (an empty residual: the draw is then from p)."""
+    shape = get_shape("tiny", vocab=vocab, n_layers=1)
+    w = gen_weights(shape, seed=37, std=0.1)
+    prompt = zipf_tokens(vocab, 30, seed=38)
+    eng = ee.Engine(shape, w, max_ctx=128, k_max=8)
+    eng.prefill(0, prompt)
+    n0, p0 = eng.seq_state(0)
+    g = np.random.default_rng(39)
+    compared = 0
+    for trial in range(24):
+        K = int(g.integers(0, 6)) if trial else 5
+        draft = zipf_tokens(vocab, K, seed=trial)
+        eng.verify(0, draft)
+        gl = eng.logits()
+        eng.rollback(0, n0, p0)
+        temp, residual = float(g.choice([0.5, 1.0, 1.7])), bool(g.integers(0, 2))
+        q = None
+        if trial % 3 == 1:
+            q = g.dirichlet(np.full(vocab, 0.5), size=K).astype(np.float32)
+        elif trial % 3 == 2:
+            q = np.stack([target_probs(gl[i], temp) for i in range(K)]).astype(np.float32) if K else \
+                np.zeros((0, vocab), np.float32)
+        eps, u = g.random(K).astype(np.float32) * 0.999, g.random(K + 1).astype(np.float32) * 0.999
+        if trial % 4 == 3:
+            eps[:] = 0.0                                # every draft token accepted: the bonus row
+        a, n = eng.verify_sample(0, draft, eps, u, q, temp, residual)
+        np.testing.assert_array_equal(eng.logits(), gl)
+        eng.rollback(0, n0, p0)
+        e64, u64 = eps.astype(np.float64), u.astype(np.float64)
+        ra, rn = accept_sample(draft, gl, e64, u64, q, temp, residual)
+        if _unique(list(draft), gl, e64, u64, q, temp, residual, 1e-12):   # float64 sums in another order
+            assert (a, n) == (ra, rn), (trial, vocab, a, n, ra, rn)
+            compared += 1
+    eng.close()
+    assert compared >= 16
