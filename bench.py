@@ -500,16 +500,16 @@ def rocprof_summary(d: str):
                 tot += st.median(v)
                 print(f"| {role} | `{names[starts[0] + j]}` | {len(v)} | {st.median(v):.2f} | {st.mean(v):.2f} |")
         print(f"| one layer (sum of medians) | | | {tot:.2f} | |")
-        # blocks of 33 rows: stage_in_kernel .. result_out_kernel; kernels busy
+        # blocks of 33 rows: stage_in_kernel or stage_embed_kernel .. accept_kernel; kernels busy
         # = the union of their intervals
         spans, busy = [], []
         i = 0
         while i < len(names):
-            if names[i] != "stage_in_kernel":
+            if not names[i].startswith("stage_"):
                 i += 1
                 continue
             j = i
-            while j < len(names) and names[j] != "result_out_kernel":
+            while j < len(names) and names[j] != "accept_kernel":
                 j += 1
             if j < len(names) and any(names[x] == "resid_kernel<1, 1>" and gy[x] == 33 for x in range(i, j)):
                 b, cur_end = 0, t0[i]
@@ -736,7 +736,7 @@ def main():
         return float(np.percentile(lat, 50)), float(np.percentile(lat, 90)), float(np.mean(acc))
 
     def select_ms(fn):
-        eng.profile(["finish", "argmax"])
+        eng.profile(["finish", "argmax", "accept"])
         eng.profile_read(reset=True)
         for _ in range(10):
             eng.rollback(0, ctx, first)

@@ -388,8 +388,9 @@ enum {
   EE_PROF_GATEUP = 5,   /* gate/up GEMM                                 */
   EE_PROF_DOWN = 6,     /* down-projection GEMM                         */
   EE_PROF_LMHEAD = 7,   /* LM-head GEMM                                 */
-  EE_PROF_ARGMAX = 8,   /* vocabulary argmax                            */
-  EE_PROF_ACCEPT = 9,   /* acceptance scan / tree walk                  */
+  EE_PROF_ARGMAX = 8,   /* top-k selection / stochastic sums            */
+  EE_PROF_ACCEPT = 9,   /* vocabulary argmax + acceptance scan or walk, */
+                        /* or the stochastic acceptance and draw        */
   EE_PROF_COMPACT = 10, /* tree KV compaction                           */
   EE_PROF_FINISH = 11,  /* GEMM epilogues: rotary + KV append, SwiGLU,  */
                         /* logits + per-chunk maxima                    */

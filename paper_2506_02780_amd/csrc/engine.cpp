@@ -313,6 +313,7 @@ void bind_work(ee_ctx* c) {
   w.verdict = reinterpret_cast<int*>(ws + L.verdict);
   w.rowstat = reinterpret_cast<double*>(ws + L.rowstat);
   w.result = reinterpret_cast<int*>(ws + L.result);
+  w.host_result = c->d_result_dst;
   unsigned char* sb = ws + L.stage;
   w.path = sb + L.s_path;
   w.tok = reinterpret_cast<int*>(sb + L.s_tok);
@@ -389,15 +390,14 @@ ee::StageCopy stage_ranges(const ee_ctx* c, const ee::Step& step) {
 }
 
 // The kernels of one block, in launch order: staging in, forward, acceptance
-// (+ tree compaction), results out.
+// with the results out (+ tree compaction).
 hipError_t launch_block(ee_ctx* c, const ee::Step& step, ee::Prof* prof, const ee::Work& w) {
   hipError_t e;
-  if ((e = ee::run_stage_in(stage_ranges(c, step), c->st)) != hipSuccess) return e;
+  if ((e = ee::run_stage_in(c->m, w, step, stage_ranges(c, step), c->st)) != hipSuccess) return e;
   if ((e = ee::run_forward(c->m, w, step, prof, c->st)) != hipSuccess) return e;
   if (step.mode == 5) return hipSuccess;
   if ((e = ee::run_accept(c->m, w, step, prof, c->st)) != hipSuccess) return e;
-  if (step.mode == 2 && (e = ee::run_compact(c->m, w, step, prof, c->st)) != hipSuccess) return e;
-  return ee::run_result_out(w, step.B, c->d_result_dst, c->st);
+  return step.mode == 2 ? ee::run_compact(c->m, w, step, prof, c->st) : hipSuccess;
 }
 
 constexpr size_t MAX_GRAPHS = 512;   // captured block shapes kept at once

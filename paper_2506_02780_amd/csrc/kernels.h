@@ -75,10 +75,11 @@ struct Work {
   float* logits;            // [Rmax, V]
   unsigned long long* amax; // [Rmax, ceil(V/2048), 8] chunk maxima (top-8 in mode 3; in mode 4
                             // then the chunk sums of the exponentials)
-  int* greedy;              // [Rmax]
+  int* greedy;              // [Rmax] mode 3: the rows' top tokens
   int* verdict;             // [Rmax] mode 3: tau | draft-accepted << 8
   double* rowstat;          // [Rmax][2] mode 4: row maximum and sum of exp((l - max) / temperature)
   int* result;              // [max_seqs][rec]: accept_len, next, accepted rows (or thresholds)
+  int* host_result;         // the same records in pinned host memory (device-visible address)
   // staged per call (host -> device)
   int* tok;                 // [Rmax]
   int* pos;                 // [Rmax] rotary position of each row
@@ -141,7 +142,7 @@ enum ProfClass {
 
 // Word ranges copied from the pinned host mirror of the staging block into the
 // device staging block by the first kernel of a block (the same word offsets
-// on both sides).
+// on both sides; range 0: the rows' tokens).
 struct StageCopy {
   const uint32_t* src;      // host mirror (device-visible address)
   uint32_t* dst;            // device staging block
@@ -149,10 +150,7 @@ struct StageCopy {
   int off[10], len[10];     // word offset and word count of each range
   int total;                // sum of the word counts
 };
-hipError_t run_stage_in(const StageCopy& sc, hipStream_t st);
-// The result records of B sequences (B * rec ints) copied from the device to
-// pinned host memory (device-visible address) by the last kernel of a block.
-hipError_t run_result_out(const Work& w, int B, int* host_result, hipStream_t st);
+hipError_t run_stage_in(const Model& m, const Work& w, const Step& s, const StageCopy& sc, hipStream_t st);
 
 hipError_t run_forward(const Model& m, const Work& w, const Step& s, Prof* prof, hipStream_t st);
 hipError_t run_accept(const Model& m, const Work& w, const Step& s, Prof* prof, hipStream_t st);

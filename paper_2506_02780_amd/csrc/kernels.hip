@@ -1468,22 +1468,20 @@ inline bool lm_head_one_slice(int d, int dt) { return d / ks_of(dt) <= FK_MAX_S;
 // FFN-side norm of the fused path is instead formed in the O projection's
 // epilogue, with sums of h^2 per 16-column tile: gemm_ep_kernel, ts_rows.)
 
+// (workgroup of chunk bx of row t, whose token is *tok)
 template <int DT, int MODE>
-__global__ __launch_bounds__(RES_THREADS) void resid_kernel(const void* __restrict__ embed,
-                                                            const int* __restrict__ tok, float* __restrict__ h,
-                                                            const float* __restrict__ part, int SK, int T,
-                                                            const float* __restrict__ gain, int d,
-                                                            void* __restrict__ xout, int x_S,
-                                                            float* __restrict__ ssq) {
+__device__ __forceinline__ void resid_block(int bx, int t, const void* __restrict__ embed, const int* tok,
+                                            float* __restrict__ h, const float* __restrict__ part, int SK, int T,
+                                            const float* __restrict__ gain, int d, void* __restrict__ xout, int x_S,
+                                            float* __restrict__ ssq) {
   __shared__ float sh[RES_THREADS / 64];
-  const int t = blockIdx.y;
-  const int col = (blockIdx.x * RES_THREADS + threadIdx.x) * 8;
+  const int col = (bx * RES_THREADS + threadIdx.x) * 8;
   float ss = 0.f;
   if (col < d) {   // d % 8 == 0: a thread's 8 columns are all in range or all out
     float* hr = h + (size_t)t * d + col;
     float v[8];
     if (MODE == 0) {
-      const size_t e0 = (size_t)tok[t] * d + col;
+      const size_t e0 = (size_t)*tok * d + col;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = load_elt<DT>(embed, e0 + e);
     } else {
@@ -1513,10 +1511,26 @@ __global__ __launch_bounds__(RES_THREADS) void resid_kernel(const void* __restri
     float r = sh[0];
 #pragma unroll
     for (int w = 1; w < RES_THREADS / 64; ++w) r += sh[w];
-    ssq[t * RES_MAX_PARTS + blockIdx.x] = r;
+    ssq[t * RES_MAX_PARTS + bx] = r;
   }
 }
 
+template <int DT, int MODE>
+__global__ __launch_bounds__(RES_THREADS) void resid_kernel(const void* __restrict__ embed,
+                                                            const int* __restrict__ tok, float* __restrict__ h,
+                                                            const float* __restrict__ part, int SK, int T,
+                                                            const float* __restrict__ gain, int d,
+                                                            void* __restrict__ xout, int x_S,
+                                                            float* __restrict__ ssq) {
+  resid_block<DT, MODE>(blockIdx.x, blockIdx.y, embed, MODE == 0 ? tok + blockIdx.y : nullptr, h, part, SK, T, gain, d,
+                        xout, x_S, ssq);
+}
+
+// Whether the kernel that stages a block's inputs also forms its first residual
+// update (stage_embed_kernel): few enough workgroups that each can read its
+// token over the host link (7B over four layers, K = 0 and 32: 394.5 -> 392.1
+// and 462.3 -> 459.5 us per step).
+inline bool stage_embeds(int d, int R) { return R * ((d + RES_COLS - 1) / RES_COLS) <= 160; }
 
 // q/k/v of row t from the QKV partials: rotary on q and k (pairs (i, i+hd/2)
 // at the row's position), q to the block buffer, k and v into the row's KV
@@ -2521,27 +2535,6 @@ __global__ __launch_bounds__(CMB_THREADS) void attn_combine_kernel(const float* 
 
 // ------------------------------------------------------- argmax and accept --
 
-__global__ __launch_bounds__(256) void argmax_kernel(const unsigned long long* __restrict__ amax,
-                                                     int n_tiles, int* __restrict__ greedy) {
-  __shared__ unsigned long long sh[256];
-  const int t = blockIdx.x;
-  unsigned long long best = 0;
-  for (int i = threadIdx.x; i < n_tiles; i += 256) {
-    const unsigned long long k = amax[(size_t)t * n_tiles + i];
-    best = k > best ? k : best;
-  }
-  sh[threadIdx.x] = best;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      const unsigned long long o = sh[threadIdx.x + w];
-      if (o > sh[threadIdx.x]) sh[threadIdx.x] = o;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) greedy[t] = (int)(0xffffffffu - (uint32_t)(sh[0] & 0xffffffffull));
-}
-
 // Value of an ordered key (inverse of amax_key; -0 comes back as +0).
 __device__ __forceinline__ float key_value(unsigned long long key) {
   const uint32_t ord = (uint32_t)(key >> 32);
@@ -2677,16 +2670,15 @@ __global__ __launch_bounds__(256) void sample_sums_kernel(const float* __restric
   if (threadIdx.x == 0) csum[(size_t)t * nchunk + blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
 }
 
-// result[0] = a, result[1] = row a's argmax (replaced by the draw), result[2..2+a)
-// = the accepted rows; rowstat[t] = (M, S).  One workgroup, one thread per row.
+// result[0] = a, result[2..2+a) = the accepted rows (resample_kernel writes
+// result[1], the draw); rowstat[t] = (M, S).  One workgroup, one thread per row.
 __global__ __launch_bounds__(256) void sample_accept_kernel(const float* __restrict__ logits,
                                                             const unsigned long long* __restrict__ amax,
                                                             const double* __restrict__ csum, int nchunk, int V,
                                                             const int* __restrict__ tok, int T,
                                                             const float* __restrict__ eps,
                                                             const unsigned char* __restrict__ sparam,
-                                                            double* __restrict__ rowstat, int* __restrict__ greedy,
-                                                            int* __restrict__ result) {
+                                                            double* __restrict__ rowstat, int* __restrict__ result) {
   __shared__ int fail;
   const SampleParams sp = *reinterpret_cast<const SampleParams*>(sparam);
   const double it = 1.0 / (double)sp.temperature;
@@ -2703,7 +2695,6 @@ __global__ __launch_bounds__(256) void sample_accept_kernel(const float* __restr
     const double M = (double)key_value(best);
     rowstat[2 * t] = M;
     rowstat[2 * t + 1] = S;
-    greedy[t] = key_index(best);
     if (t < K) {
       const int d = tok[t + 1];
       const double pd = sample_exp(logits[(size_t)t * V + d], M, it) / S;
@@ -2787,7 +2778,8 @@ __global__ __launch_bounds__(256) void resample_kernel(const float* __restrict__
                                                        const float* __restrict__ unif,
                                                        const unsigned char* __restrict__ sparam,
                                                        const double* __restrict__ rowstat,
-                                                       const double* __restrict__ gsum, int* __restrict__ result) {
+                                                       const double* __restrict__ gsum, int* __restrict__ result,
+                                                       int* host) {
   __shared__ double gs[SAMPLE_MAX_GROUPS];
   __shared__ double wsum[4];
   __shared__ int pick, last;
@@ -2865,38 +2857,72 @@ __global__ __launch_bounds__(256) void resample_kernel(const float* __restrict__
     int chosen;
     if (over) chosen = g * 64 + (__ffsll((long long)over) - 1);
     else chosen = pos ? g * 64 + (63 - __clzll((long long)pos)) : g * 64;
-    if (lane == 0) result[1] = chosen;
+    if (lane == 0) {   // the host's record (pinned memory): the caller reads a and the token
+      result[1] = chosen;
+      host[0] = r.a;
+      host[1] = chosen;
+      __threadfence_system();
+    }
   }
 }
 
+// The end of a block, one workgroup per sequence: every row's greedy token (the
+// largest of its chunk maxima, 16 lanes a row; mode 3: found by
+// topk_select_kernel), then the acceptance by the first wave, written to the
+// device's record and to the host's (pinned memory, device-visible address).
 // result[0] = accepted rows a, result[1] = next token, result[2..2+a) = accepted
 // block rows in depth order (mode 3: result[2..2+K) = the threshold tau of
-// every draft row).  Mode 0 (prefill) commits every row.
-__global__ __launch_bounds__(64) void accept_kernel(const int* __restrict__ tok,
-                                                    const int* __restrict__ prow,
-                                                    const int* __restrict__ greedy,
-                                                    const int* __restrict__ verdict, int T, int mode,
-                                                    int* __restrict__ result, int rec) {
+// every draft row).  Mode 0 (prefill) commits every row.  Launches bound this:
+// as three kernels (argmax, acceptance, copy to the host) a block took about
+// 4 us more (7B over four layers, K = 0: 399.1 -> 394.5 us).
+constexpr int ACC_THREADS = 512;
+constexpr int ACC_MAX_T = 513;   // rows per sequence (k_max <= 512)
+
+__global__ __launch_bounds__(ACC_THREADS) void accept_kernel(const unsigned long long* __restrict__ amax, int nchunk,
+                                                             const int* __restrict__ tok,
+                                                             const int* __restrict__ prow,
+                                                             const int* __restrict__ greedy_in,
+                                                             const int* __restrict__ verdict, int T, int mode,
+                                                             int* __restrict__ result, int* host, int rec) {
+  __shared__ int greedy[ACC_MAX_T];
   // workgroup b: sequence b, rows b*T .. b*T + T - 1, result record b (rec ints)
-  tok += blockIdx.x * T;
-  prow += blockIdx.x * T;
-  greedy += blockIdx.x * T;
-  verdict += blockIdx.x * T;
+  const int row0 = blockIdx.x * T;
+  tok += row0;
+  prow += row0;
+  verdict += row0;
   result += blockIdx.x * rec;
+  host += blockIdx.x * rec;
+  if (mode == 3) {
+    for (int t = threadIdx.x; t < T; t += ACC_THREADS) greedy[t] = greedy_in[row0 + t];
+  } else {
+    const int sub = threadIdx.x & 15;
+    for (int t = mode == 0 ? T - 1 : 0; t < T; t += ACC_THREADS / 16) {   // (prefill: only the last row's)
+      const int r = t + (int)(threadIdx.x >> 4);
+      unsigned long long best = 0;
+      if (r < T)
+        for (int i = sub; i < nchunk; i += 16) best = max(best, amax[(size_t)(row0 + r) * nchunk + i]);
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) best = max(best, (unsigned long long)__shfl_xor(best, o));
+      if (r < T && sub == 0) greedy[r] = (int)(0xffffffffu - (uint32_t)(best & 0xffffffffull));
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
   const int lane = threadIdx.x;
   const int K = T - 1;
+  auto put = [&](int i, int v) {
+    result[i] = v;
+    host[i] = v;
+  };
   if (mode == 0) {
     if (lane == 0) {
-      result[0] = T - 1;
-      result[1] = greedy[T - 1];
+      put(0, T - 1);
+      put(1, greedy[T - 1]);
     }
-    return;
-  }
-  if (mode == 1 || mode == 3) {
+  } else if (mode == 1 || mode == 3) {
     // draft d_{i+1} (row i+1) is checked against row i: its greedy token
-    // (mode 1) or its verdict (mode 3: top-k); the first
-    // failing row, found 64 rows at a time, is a.  Mode 3 also records every
-    // row's threshold.
+    // (mode 1) or its verdict (mode 3: top-k); the first failing row, found 64
+    // rows at a time, is a.  Mode 3 also records every row's threshold.
     int a = K;
     for (int i0 = 0; i0 < K; i0 += 64) {
       const int i = i0 + lane;
@@ -2907,7 +2933,7 @@ __global__ __launch_bounds__(64) void accept_kernel(const int* __restrict__ tok,
         } else {
           const int vd = verdict[i];
           fails = !((vd >> 8) & 1);
-          result[2 + i] = vd & 0xff;
+          put(2 + i, vd & 0xff);
         }
       }
       const unsigned long long b = __ballot(fails);
@@ -2915,28 +2941,29 @@ __global__ __launch_bounds__(64) void accept_kernel(const int* __restrict__ tok,
       if (mode != 3 && a != K) break;
     }
     if (lane == 0) {
-      result[0] = a;
-      result[1] = greedy[a];
+      put(0, a);
+      put(1, greedy[a]);
     }
     if (mode != 3)
-      for (int i = lane; i < a; i += 64) result[2 + i] = i + 1;
-    return;
+      for (int i = lane; i < a; i += 64) put(2 + i, i + 1);
+  } else {
+    // tree walk from row 0 (trees have at most 64 nodes)
+    int cur = 0, a = 0;
+    for (;;) {
+      const bool hit = lane < K && prow[lane + 1] == cur && tok[lane + 1] == greedy[cur];
+      const unsigned long long b = __ballot(hit);
+      if (!b) break;
+      const int row = __ffsll((long long)b);   // lowest node index i -> row i + 1
+      if (lane == 0) put(2 + a, row);
+      cur = row;
+      ++a;
+    }
+    if (lane == 0) {
+      put(0, a);
+      put(1, greedy[cur]);
+    }
   }
-  // tree walk from row 0 (trees have at most 64 nodes)
-  int cur = 0, a = 0;
-  for (;;) {
-    const bool hit = lane < K && prow[lane + 1] == cur && tok[lane + 1] == greedy[cur];
-    const unsigned long long b = __ballot(hit);
-    if (!b) break;
-    const int row = __ffsll((long long)b);   // lowest node index i -> row i + 1
-    if (lane == 0) result[2 + a] = row;
-    cur = row;
-    ++a;
-  }
-  if (lane == 0) {
-    result[0] = a;
-    result[1] = greedy[cur];
-  }
+  __threadfence_system();
 }
 
 // Move K/V of accepted tree rows to consecutive slots n+1.. in depth order.
@@ -3085,7 +3112,7 @@ static hipError_t forward_t(const Model& m, const Work& w, const Step& s, Prof* 
     return hipMemcpyAsync(s.cap + (size_t)l * c_layer + off, src, bytes, hipMemcpyDeviceToDevice, st);
   };
 
-  if ((e = timed(prof, PC_NORM, st, [&] {
+  if (!stage_embeds(d, R) && (e = timed(prof, PC_NORM, st, [&] {
          hipLaunchKernelGGL((resid_kernel<DT, 0>), dim3((d + RES_COLS - 1) / RES_COLS, R), dim3(RES_THREADS), 0, st,
                             m.embed, w.tok, w.h, w.part, 1, R, m.layers[0].attn_gain, d, (void*)w.xbuf, Sd, w.ssq);
          return last();
@@ -3269,15 +3296,14 @@ static hipError_t forward_t(const Model& m, const Work& w, const Step& s, Prof* 
          return last();
        })) != hipSuccess)
     return e;
+  if (!topk && s.mode != 4) return hipSuccess;   // (accept_kernel takes the rows' argmax itself)
   return timed(prof, PC_ARGMAX, st, [&] {
     if (topk)
       hipLaunchKernelGGL(topk_select_kernel, dim3(R), dim3(64), 0, st, w.amax, nchunk, w.tok, w.info, s.T,
                          w.greedy, w.verdict);
-    else if (s.mode == 4)   // (chunk sums behind the chunk maxima, whose buffer has room for 8 keys per chunk)
+    else   // (chunk sums behind the chunk maxima, whose buffer has room for 8 keys per chunk)
       hipLaunchKernelGGL(sample_sums_kernel, dim3(nchunk, R), dim3(256), 0, st, w.logits, w.amax, nchunk, m.V,
                          w.sparam, reinterpret_cast<double*>(w.amax + (size_t)R * nchunk));
-    else
-      hipLaunchKernelGGL(argmax_kernel, dim3(R), dim3(256), 0, st, w.amax, nchunk, w.greedy);
     return last();
   });
 }
@@ -3285,33 +3311,53 @@ static hipError_t forward_t(const Model& m, const Work& w, const Step& s, Prof* 
 // ------------------------------------------------------------ host staging --
 //
 // The per-call inputs are read straight from pinned host memory and the
-// result records written straight back to it by kernels of the block itself,
-// so a block waits on no copy-engine transfer before its first kernel or
-// after its last.
+// result records written straight back to it by kernels of the block itself
+// (accept_kernel, resample_kernel), so a block waits on no copy-engine transfer
+// before its first kernel or after its last.
 
-__global__ __launch_bounds__(256) void stage_in_kernel(StageCopy sc) {
-  int i = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void stage_words(const StageCopy& sc, int i) {
   if (i >= sc.total) return;
   int r = 0;
   while (r + 1 < sc.n && i >= sc.len[r]) i -= sc.len[r++];
   sc.dst[sc.off[r] + i] = sc.src[sc.off[r] + i];
 }
 
-__global__ __launch_bounds__(256) void result_out_kernel(const int* __restrict__ src, int* dst, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) dst[i] = src[i];
-  __threadfence_system();
+__global__ __launch_bounds__(256) void stage_in_kernel(StageCopy sc) { stage_words(sc, blockIdx.x * 256 + threadIdx.x); }
+
+// Staging and the first residual update in one launch: workgroups 0 .. nx R - 1
+// read their row's token from the host mirror themselves (range 0 of the
+// staged words), the others copy.
+template <int DT>
+__global__ __launch_bounds__(RES_THREADS) void stage_embed_kernel(StageCopy sc, const void* __restrict__ embed,
+                                                                  float* __restrict__ h,
+                                                                  const float* __restrict__ gain, int d,
+                                                                  void* __restrict__ xout, int x_S,
+                                                                  float* __restrict__ ssq, int nx, int R) {
+  const int b = blockIdx.x;
+  if (b < nx * R) {
+    const int t = b / nx;
+    resid_block<DT, 0>(b - t * nx, t, embed, reinterpret_cast<const int*>(sc.src + sc.off[0]) + t, h, nullptr, 1, R,
+                       gain, d, xout, x_S, ssq);
+  } else {
+    stage_words(sc, (b - nx * R) * RES_THREADS + threadIdx.x);
+  }
 }
 
-hipError_t run_stage_in(const StageCopy& sc, hipStream_t st) {
+hipError_t run_stage_in(const Model& m, const Work& w, const Step& s, const StageCopy& sc, hipStream_t st) {
   if (sc.total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(stage_in_kernel, dim3((sc.total + 255) / 256), dim3(256), 0, st, sc);
-  return hipGetLastError();
-}
-
-hipError_t run_result_out(const Work& w, int B, int* host_result, hipStream_t st) {
-  const int n = B * w.rec;
-  hipLaunchKernelGGL(result_out_kernel, dim3((n + 255) / 256), dim3(256), 0, st, w.result, host_result, n);
+  const int R = s.T * s.B;
+  if (stage_embeds(m.d, R)) {
+    const int nx = (m.d + RES_COLS - 1) / RES_COLS;
+    const dim3 grid(nx * R + (sc.total + RES_THREADS - 1) / RES_THREADS);
+    if (m.dt == DT_BF16)
+      hipLaunchKernelGGL(stage_embed_kernel<DT_BF16>, grid, dim3(RES_THREADS), 0, st, sc, m.embed, w.h,
+                         m.layers[0].attn_gain, m.d, (void*)w.xbuf, m.d / ks_of(m.dt), w.ssq, nx, R);
+    else
+      hipLaunchKernelGGL(stage_embed_kernel<DT_F32>, grid, dim3(RES_THREADS), 0, st, sc, m.embed, w.h,
+                         m.layers[0].attn_gain, m.d, (void*)w.xbuf, m.d / ks_of(m.dt), w.ssq, nx, R);
+  } else {
+    hipLaunchKernelGGL(stage_in_kernel, dim3((sc.total + 255) / 256), dim3(256), 0, st, sc);
+  }
   return hipGetLastError();
 }
 
@@ -3324,20 +3370,22 @@ hipError_t run_forward(const Model& m, const Work& w, const Step& s, Prof* prof,
 
 hipError_t run_accept(const Model& m, const Work& w, const Step& s, Prof* prof, hipStream_t st) {
   return timed(prof, PC_ACCEPT, st, [&] {
+    const int nchunk = (m.V + 2047) / 2048;
     if (s.mode == 4) {   // one sequence: acceptance, then the draw at the accepted length
-      const int nchunk = (m.V + 2047) / 2048, ng = (m.V + 63) / 64;
+      const int ng = (m.V + 63) / 64;
       double* csum = reinterpret_cast<double*>(w.amax + (size_t)s.T * nchunk);
       double* gsum = reinterpret_cast<double*>(w.part);   // (the GEMM partials are consumed: at least 4 V bytes)
       hipLaunchKernelGGL(sample_accept_kernel, dim3(1), dim3(256), 0, st, w.logits, w.amax, csum, nchunk, m.V, w.tok,
-                         s.T, w.eps, w.sparam, w.rowstat, w.greedy, w.result);
+                         s.T, w.eps, w.sparam, w.rowstat, w.result);
       hipLaunchKernelGGL(resample_sums_kernel, dim3((ng + RSUM_GROUPS - 1) / RSUM_GROUPS), dim3(256), 0, st, w.logits,
                          m.V, w.tok, s.T, w.sparam, w.rowstat, w.result, gsum);
       hipLaunchKernelGGL(resample_kernel, dim3(1), dim3(256), 0, st, w.logits, m.V, w.tok, s.T, w.unif, w.sparam,
-                         w.rowstat, gsum, w.result);
+                         w.rowstat, gsum, w.result, w.host_result);
       return hipGetLastError();
     }
-    hipLaunchKernelGGL(accept_kernel, dim3(s.B), dim3(64), 0, st, w.tok, w.prow, w.greedy, w.verdict, s.T,
-                       s.mode, w.result, w.rec);
+    if (s.T > ACC_MAX_T) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(accept_kernel, dim3(s.B), dim3(ACC_THREADS), 0, st, w.amax, nchunk, w.tok, w.prow, w.greedy,
+                       w.verdict, s.T, s.mode, w.result, w.host_result, w.rec);
     return hipGetLastError();
   });
 }
