@@ -174,7 +174,7 @@ hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t st)
 
 // -------------------------------------------------------------------- GEMM --
 //
-// Y[t, n] = sum_k X[t, k] W[n, k] for T <= 80 rows, split over K:
+// Y[t, n] = sum_k X[t, k] W[n, k], split over K:
 //   * the reduction dimension (S super-steps of KS columns) is cut into SK
 //     slices of SS super-steps; SK depends only on (N, K);
 //   * a workgroup (8 waves) owns one slice and a set of 16-feature tiles;
@@ -233,7 +233,11 @@ inline int gemm_slices(int S) {
 // side by side, so one of them fetches each weight tile from HBM and the
 // others find it in that XCD's L2.  NT: non-temporal weight loads (one row
 // group: nothing re-reads them).
-template <int DT, int MT, bool NT>
+// SPW: super-steps per wave and slice it has registers for.  What a CU takes in
+// per matrix instruction falls with MT, and the 256 registers of a lane hold
+// SPW x MT input fragments and two tiles of weights: 5 row tiles at 8
+// super-steps, 6 at 7, 7 at 6, 8 at 5 (gemm_row_tiles).
+template <int DT, int MT, int SPW, bool NT>
 __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_kernel(GemmArgs a) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 15;
   const int rg = blockIdx.x / a.P, q = blockIdx.x - rg * a.P;
@@ -245,9 +249,9 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_kernel(GemmArgs a) {
   const auto ws = make_rsrc(a.w, (unsigned)((size_t)a.n_tiles * S * 1024));
   const auto ps = make_rsrc(a.part, (unsigned)((size_t)a.SK * a.Ttot * a.N * 4));
   constexpr int WAUX = NT ? 2 : 0;
-  uint4 xr[GEMM_SPW][MT];
+  uint4 xr[SPW][MT];
 #pragma unroll
-  for (int i = 0; i < GEMM_SPW; ++i) {
+  for (int i = 0; i < SPW; ++i) {
     const int sl = wv + GEMM_WAVES * i;
 #pragma unroll
     for (int m = 0; m < MT; ++m)
@@ -266,12 +270,12 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_kernel(GemmArgs a) {
   const int qq = threadIdx.x % (MT * 64);
   const bool qown = threadIdx.x < MT * 64;
   const int rm = qq >> 6, rl = qq & 63, rt = rm * 16 + (rl & 15);
-  auto tile_step = [&](const uint4 (&wf)[GEMM_SPW], int tile, int pb) {
+  auto tile_step = [&](const uint4 (&wf)[SPW], int tile, int pb) {
     f32x4 acc[MT];
 #pragma unroll
     for (int m = 0; m < MT; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < GEMM_SPW; ++i)
+    for (int i = 0; i < SPW; ++i)
 #pragma unroll
       for (int m = 0; m < MT; ++m) acc[m] = mma<DT>(wf[i], xr[i][m], acc[m]);
 #pragma unroll
@@ -288,12 +292,12 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_kernel(GemmArgs a) {
   // two named weight buffers: the next tile's fragments are requested before
   // the current tile is computed, and no in-flight register is ever copied
   int tile = q / a.SK;
-  uint4 wa[GEMM_SPW], wb[GEMM_SPW];
+  uint4 wa[SPW], wb[SPW];
   if (MT == 1) {
     // one row tile: inputs and the first tile's weights requested super-step
     // by super-step, in the order the first MFMAs use them
 #pragma unroll
-    for (int i = 0; i < GEMM_SPW; ++i) {
+    for (int i = 0; i < SPW; ++i) {
       const int sl = wv + GEMM_WAVES * i;
       xr[i][0] = bload<0>(xs, (sl < ns && c < T) ? (unsigned)(((s0 + sl) * 64 + lane) * 16) : OOB);
       wa[i] = wload(tile, i);
@@ -301,27 +305,48 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_kernel(GemmArgs a) {
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < GEMM_SPW; ++i) wa[i] = wload(tile, i);
+    for (int i = 0; i < SPW; ++i) wa[i] = wload(tile, i);
   }
   for (;;) {
 #pragma unroll
-    for (int i = 0; i < GEMM_SPW; ++i) wb[i] = wload(tile + groups, i);
+    for (int i = 0; i < SPW; ++i) wb[i] = wload(tile + groups, i);
     tile_step(wa, tile, 0);
     tile += groups;
     if (tile >= a.n_tiles) break;
 #pragma unroll
-    for (int i = 0; i < GEMM_SPW; ++i) wa[i] = wload(tile + groups, i);
+    for (int i = 0; i < SPW; ++i) wa[i] = wload(tile + groups, i);
     tile_step(wb, tile, 1);
     tile += groups;
     if (tile >= a.n_tiles) break;
   }
 }
 
-constexpr int GEMM_MAX_ROWS = 80;   // rows one workgroup holds in registers (MT <= 5)
+// Row tiles one workgroup can hold for slices of SS super-steps.
+inline int gemm_row_tiles(int SS) {
+  const int spw = (SS + GEMM_WAVES - 1) / GEMM_WAVES;
+  return spw <= 5 ? 8 : spw == 6 ? 7 : spw == 7 ? 6 : 5;
+}
 
-// Y = X W^T for R rows.  Up to 80 rows: one row group, one workgroup per CU,
-// each streaming its weight tiles once.  More rows: groups of 80 rows in
-// the same launch, sharing each weight stream through L2.  A row's
+template <int DT, bool NT>
+static hipError_t launch_gemm(const GemmArgs& a, int mt, dim3 grid, hipStream_t st) {
+  const dim3 block(GEMM_WAVES * 64);
+  switch (mt) {
+    case 1: hipLaunchKernelGGL((gemm_kernel<DT, 1, 8, NT>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((gemm_kernel<DT, 2, 8, NT>), grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((gemm_kernel<DT, 3, 8, NT>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((gemm_kernel<DT, 4, 8, NT>), grid, block, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((gemm_kernel<DT, 5, 8, NT>), grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((gemm_kernel<DT, 6, 7, NT>), grid, block, 0, st, a); break;
+    case 7: hipLaunchKernelGGL((gemm_kernel<DT, 7, 6, NT>), grid, block, 0, st, a); break;
+    case 8: hipLaunchKernelGGL((gemm_kernel<DT, 8, 5, NT>), grid, block, 0, st, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// Y = X W^T for R rows: as few row groups as the registers allow, of equal row
+// tiles, in one launch.  One group: one workgroup per CU, each streaming its
+// weight tiles once.  More: they share each weight stream through L2.  A row's
 // arithmetic is the same either way (and the same as in a launch of its own).
 template <int DT>
 static hipError_t gemm(const uint4* w, const uint4* x, int N, int K, int R, float* part,
@@ -332,28 +357,17 @@ static hipError_t gemm(const uint4* w, const uint4* x, int N, int K, int R, floa
   a.SK = gemm_slices(a.S);
   a.SS = (a.S + a.SK - 1) / a.SK;
   a.n_tiles = N / 16;
-  const dim3 block(GEMM_WAVES * 64);
-  if (R <= GEMM_MAX_ROWS) {
+  const int nrt = (R + 15) / 16, most = gemm_row_tiles(a.SS), rg = (nrt + most - 1) / most, mt = (nrt + rg - 1) / rg;
+  if (rg == 1) {
     a.rows = R;
     a.G = std::max(1, std::min(256 / a.SK, a.n_tiles));
     a.P = a.G * a.SK;
-    const dim3 grid(a.P);
-    switch ((R + 15) / 16) {
-      case 1: hipLaunchKernelGGL((gemm_kernel<DT, 1, true>), grid, block, 0, st, a); break;
-      case 2: hipLaunchKernelGGL((gemm_kernel<DT, 2, true>), grid, block, 0, st, a); break;
-      case 3: hipLaunchKernelGGL((gemm_kernel<DT, 3, true>), grid, block, 0, st, a); break;
-      case 4: hipLaunchKernelGGL((gemm_kernel<DT, 4, true>), grid, block, 0, st, a); break;
-      case 5: hipLaunchKernelGGL((gemm_kernel<DT, 5, true>), grid, block, 0, st, a); break;
-      default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return launch_gemm<DT, true>(a, mt, dim3(a.P), st);
   }
-  a.rows = GEMM_MAX_ROWS;
-  const int rg = (R + GEMM_MAX_ROWS - 1) / GEMM_MAX_ROWS;
+  a.rows = 16 * mt;
   a.P = std::max(256 / rg / 8 * 8, (a.SK + 7) / 8 * 8);
   a.G = std::max(1, std::min(a.P / a.SK, a.n_tiles));
-  hipLaunchKernelGGL((gemm_kernel<DT, 5, false>), dim3(rg * a.P), block, 0, st, a);
-  return hipGetLastError();
+  return launch_gemm<DT, false>(a, mt, dim3(rg * a.P), st);
 }
 
 constexpr int MAX_SLICES = 16;   // gemm_slices() never exceeds this for K <= 32768
