@@ -327,21 +327,33 @@ inline int gemm_row_tiles(int SS) {
   return spw <= 5 ? 8 : spw == 6 ? 7 : spw == 7 ? 6 : 5;
 }
 
+// (mt row tiles, spw super-steps per wave: the smallest instance that holds
+// them, since a super-step that is not there still costs its matrix
+// instructions and the issue of its loads)
+template <int DT, bool NT, int MT>
+static hipError_t launch_gemm_mt(const GemmArgs& a, int spw, dim3 grid, hipStream_t st) {
+  const dim3 block(GEMM_WAVES * 64);
+  if (spw <= 5) hipLaunchKernelGGL((gemm_kernel<DT, MT, 5, NT>), grid, block, 0, st, a);
+  else if (MT <= 7 && spw == 6) hipLaunchKernelGGL((gemm_kernel<DT, MT <= 7 ? MT : 7, 6, NT>), grid, block, 0, st, a);
+  else if (MT <= 6 && spw == 7) hipLaunchKernelGGL((gemm_kernel<DT, MT <= 6 ? MT : 6, 7, NT>), grid, block, 0, st, a);
+  else if (MT <= 5 && spw == 8) hipLaunchKernelGGL((gemm_kernel<DT, MT <= 5 ? MT : 5, 8, NT>), grid, block, 0, st, a);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
 template <int DT, bool NT>
 static hipError_t launch_gemm(const GemmArgs& a, int mt, dim3 grid, hipStream_t st) {
-  const dim3 block(GEMM_WAVES * 64);
+  const int spw = (a.SS + GEMM_WAVES - 1) / GEMM_WAVES;
   switch (mt) {
-    case 1: hipLaunchKernelGGL((gemm_kernel<DT, 1, 8, NT>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((gemm_kernel<DT, 2, 8, NT>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((gemm_kernel<DT, 3, 8, NT>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((gemm_kernel<DT, 4, 8, NT>), grid, block, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((gemm_kernel<DT, 5, 8, NT>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((gemm_kernel<DT, 6, 7, NT>), grid, block, 0, st, a); break;
-    case 7: hipLaunchKernelGGL((gemm_kernel<DT, 7, 6, NT>), grid, block, 0, st, a); break;
-    case 8: hipLaunchKernelGGL((gemm_kernel<DT, 8, 5, NT>), grid, block, 0, st, a); break;
-    default: return hipErrorInvalidValue;
+    case 1: if constexpr (NT) return launch_gemm_mt<DT, NT, 1>(a, spw, grid, st); else return hipErrorInvalidValue;
+    case 2: if constexpr (NT) return launch_gemm_mt<DT, NT, 2>(a, spw, grid, st); else return hipErrorInvalidValue;
+    case 3: return launch_gemm_mt<DT, NT, 3>(a, spw, grid, st);
+    case 4: return launch_gemm_mt<DT, NT, 4>(a, spw, grid, st);
+    case 5: return launch_gemm_mt<DT, NT, 5>(a, spw, grid, st);
+    case 6: return launch_gemm_mt<DT, NT, 6>(a, spw, grid, st);
+    case 7: return launch_gemm_mt<DT, NT, 7>(a, spw, grid, st);
+    case 8: return launch_gemm_mt<DT, NT, 8>(a, spw, grid, st);
+    default: return hipErrorInvalidValue;   // (several groups have at least three row tiles each)
   }
-  return hipGetLastError();
 }
 
 // Y = X W^T for R rows: as few row groups as the registers allow, of equal row
