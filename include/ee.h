@@ -106,9 +106,9 @@ int32_t ee_create(const ee_model_config* cfg, const ee_weights* w, void* packed,
 int32_t ee_destroy(ee_ctx* ctx);
 
 /* Run the prompt tokens[0..n-1] of sequence `seq` (which must be empty),
- * commit all n positions to the KV cache (the last block holds the
- * (n - 1) % (k_max + 1) + 1 last rows, the ones before it run in blocks of up
- * to max(k_max + 1, 512) rows; results do not depend on the blocks) and
+ * commit all n positions to the KV cache (in blocks of up to
+ * max(k_max + 1, 512) rows; results do not depend on the blocks, and
+ * ee_get_logits reads the last (n - 1) % (k_max + 1) + 1 rows) and
  * return the greedy token of the last row in *next_token: the first emitted
  * token of plain greedy decoding (Eq. 1, the argmax of the target's
  * distribution given the prompt), now "pending" (emitted, not yet run through
@@ -319,8 +319,9 @@ int32_t ee_edit_step(ee_ctx* target, int32_t seq, ee_ctx* draft, int32_t draft_s
                      ee_edit_state* state, int32_t* out, int32_t n_out, int32_t out_cap,
                      int32_t* n_new);
 
-/* Copy the logits of the last prefill block or verify block (rows x vocab,
- * fp32, row-major) to host memory; rows must equal that block's row count.
+/* Copy the logits of the last verify block, or of the last rows of the last
+ * prompt or extension (ee_prefill), as rows x vocab fp32, row-major, to host
+ * memory; rows must equal that row count.
  * Test and inspection aid; not needed on the hot path. */
 int32_t ee_get_logits(ee_ctx* ctx, float* host_out, int32_t rows);
 

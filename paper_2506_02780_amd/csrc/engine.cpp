@@ -142,7 +142,7 @@ size_t partial_cols(const ee_model_config& g, bool lm_head = true) {
   return mx;
 }
 
-// Rows of the commit-only blocks of prompts and extensions: up to 512 whatever
+// Rows of the blocks of prompts and extensions: up to 512 whatever
 // k_max is, since a block streams every weight once for all of its rows (1B,
 // 1000 tokens, k_max 64: 14.25 ms in 65-row blocks, 5.0 ms in blocks of 512,
 // 463 and 25 rows), halved until the block's attention states, GEMM
@@ -151,6 +151,7 @@ size_t partial_cols(const ee_model_config& g, bool lm_head = true) {
 int prompt_rows(const ee_model_config& g) {
   const int Tmax = g.k_max + 1;
   const size_t splits = (g.max_ctx + SPLIT - 1) / SPLIT + 1;
+  if (partial_cols(g) * (Tmax + 15) * 4 >= (size_t(1) << 31)) return Tmax;
   for (int p = std::min(512, (g.max_ctx + 15) / 16 * 16); p > Tmax; p = p / 2 / 16 * 16)
     if (splits * g.n_heads * p * (g.head_dim + 2) * 4 < (size_t(1) << 31) &&
         partial_cols(g, false) * p * 4 < (size_t(1) << 31) && g.n_heads / g.n_kv_heads * p <= 64 * 16 * 16)
@@ -202,8 +203,9 @@ Layout make_layout(const ee_model_config* c) {
   L.zbuf = o; o += up(Tpad * F * esz);
   L.q = o; o += up(Rall * H * hd * esz);
   L.part = o; o += up((size_t)L.max_splits * Hkv * Rall * L.G * (hd + 2) * 4);
-  // split-K partials of the largest GEMM: [slices][rows][N]
-  L.gpart = o; o += up(std::max(partial_cols(*c) * L.Rmax, partial_cols(*c, false) * Rall) * 4);
+  // split-K partials of the largest GEMM: [slices][rows][N] (the LM head of a
+  // prompt block: its last rows from the start of their row tile)
+  L.gpart = o; o += up(std::max(partial_cols(*c) * std::max(L.Rmax, L.Tmax + 15), partial_cols(*c, false) * Rall) * 4);
   L.logits = o; o += up(L.Rmax * V * 4);
   L.amax = o; o += up(L.Rmax * ((V + 2047) / 2048) * 8 * 8);
   L.greedy = o; o += up(L.Rmax * 4);
@@ -460,8 +462,9 @@ int order_after_user(ee_ctx* c) {
 // given for every sequence.
 // `scratch_work`: buffers of the block when they are not the context's own
 // (ee_verify_noalloc); such a block runs without graph replay.
+// `head`: rows at the end of a prefill block whose logits are computed (0: all).
 int run_block(ee_ctx* c, Seq* const* seqs, int B, int T, int mode, int top_k = 0, int dynamic = 0,
-              const ee::Work* scratch_work = nullptr) {
+              const ee::Work* scratch_work = nullptr, int head = 0) {
   const Layout& L = c->lay;
   int* ptab = reinterpret_cast<int*>(c->h_stage + L.s_ptable);
   int* info = reinterpret_cast<int*>(c->h_stage + L.s_info);
@@ -490,12 +493,13 @@ int run_block(ee_ctx* c, Seq* const* seqs, int B, int T, int mode, int top_k = 0
   if (rc) return rc;
   ee::Step step{T, B, mode, splits};
   step.cap = c->cap;
+  step.head = head;
   ee::Prof* prof = c->prof.mask ? &c->prof : nullptr;
   // events recorded by graph nodes cannot be timed, and captures are copies
-  // of a test aid: profiled or captured blocks run eagerly; so do commit-only
-  // blocks, whose row counts follow the prompt's length (a graph per length
+  // of a test aid: profiled or captured blocks run eagerly; so do the
+  // blocks of longer prompts, whose row counts follow the prompt's length (a graph per length
   // would be captured again and again) and whose launches run ahead of the GPU
-  const bool eager = prof || c->cap || scratch_work || mode == 5;
+  const bool eager = prof || c->cap || scratch_work || mode == 5 || head;
   const ee_ctx::Captured* cg = eager ? nullptr : block_graph(c, step, nullptr);
   if (cg) {
     HIP_TRY(c, hipGraphLaunch(cg->exec, c->st));
@@ -517,7 +521,7 @@ int run_block(ee_ctx* c, Seq* const* seqs, int B, int T, int mode, int top_k = 0
     c->prof_ms[c->ev_cls[i]] += ms;
     c->prof_n[c->ev_cls[i]] += 1;
   }
-  if (mode != 5) c->last_T = B * T;   // (a commit-only block leaves the last logits)
+  if (mode != 5) c->last_T = head ? head : B * T;   // (a commit-only block leaves the last logits)
   return EE_OK;
 }
 
@@ -564,14 +568,14 @@ void stage_draft(ee_ctx* c, int b, int T, const Seq& s, const int32_t* draft, co
 }
 
 // Run rows[0..n) at positions len.. and commit all of them (every row's K/V
-// kept); *last = the greedy token of the final row.  The last block has the
-// rows left over by whole blocks of k_max + 1 (at least one): only its logits
-// can be read, so the rows before it run in commit-only blocks of up to Pmax
-// rows, which stop once their keys and values are in the cache: no final layer
-// past its QKV projection, no LM head (312 us per 513-row block at the 7B
-// width).  A row's arithmetic does not depend on its block.  (A rounding-site
-// capture records whole blocks of at most k_max + 1 rows.)  On failure the
-// sequence is left as it was.
+// kept); *last = the greedy token of the final row.  ee_get_logits reads the
+// rows left over by whole blocks of k_max + 1 (at least one): the `tail`.  The
+// rows run in blocks of up to Pmax; the blocks before the last stop once their
+// keys and values are in the cache (no final layer past its QKV projection, no
+// LM head: 312 us per 513-row block at the 7B width), and the last one, which
+// holds the whole tail, runs the LM head for the tail only.  A row's arithmetic
+// does not depend on its block.  (A rounding-site capture records whole blocks
+// of at most k_max + 1 rows.)  On failure the sequence is left as it was.
 int commit_rows(ee_ctx* c, Seq& s, const int32_t* rows, int n, int* last) {
   const Layout& L = c->lay;
   int added;
@@ -579,19 +583,20 @@ int commit_rows(ee_ctx* c, Seq& s, const int32_t* rows, int n, int* last) {
   int* tok = reinterpret_cast<int*>(c->h_stage + L.s_tok);
   int* pos = reinterpret_cast<int*>(c->h_stage + L.s_pos);
   int* prow = reinterpret_cast<int*>(c->h_stage + L.s_prow);
-  const int len0 = s.len, lead = (n - 1) / L.Tmax * L.Tmax;   // rows before the last block
+  const int len0 = s.len, tail = (n - 1) % L.Tmax + 1;
   const int most = c->cap ? L.Tmax : std::max(L.Tmax, L.Pmax);
   int T;
   for (int off = 0; off < n; off += T) {
-    const bool final = off >= lead;
-    T = final ? n - off : std::min(most, lead - off);
+    T = std::min(most, n - off);
+    if (n - off - T > 0 && n - off - T < tail) T = n - off - tail;   // the last block holds the tail
+    const bool final = off + T == n;
     for (int r = 0; r < T; ++r) {
       tok[r] = rows[off + r];
       pos[r] = s.len + r;
       prow[r] = r - 1;
     }
     Seq* one = &s;
-    const int rc = run_block(c, &one, 1, T, final || c->cap ? 0 : 5);
+    const int rc = run_block(c, &one, 1, T, final || c->cap ? 0 : 5, 0, 0, nullptr, final && T > tail ? tail : 0);
     if (rc) {
       s.len = len0;
       unreserve(c, s, added);

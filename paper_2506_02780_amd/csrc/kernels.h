@@ -128,6 +128,8 @@ struct Step {
                 // rows' keys and values (no logits, no result)
   int splits;   // attention splits of the grid: the most any sequence of the
                 // block uses, ceil((n + T) / 256); 1 .. max_splits
+  int head = 0; // rows at the end of a one-sequence prefill block whose logits
+                // are computed (0: all)
   unsigned char* cap = nullptr;   // test aid: copies of every rounding site's
                                   // values (capture_bytes(m, T * B) bytes), or null
 };

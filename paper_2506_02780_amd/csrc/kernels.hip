@@ -1701,7 +1701,7 @@ __global__ __launch_bounds__(256) void logits_kernel(const float* __restrict__ p
                                                      float* __restrict__ logits,
                                                      unsigned long long* __restrict__ amax, int nchunk,
                                                      const float* __restrict__ ssq, int d, float eps) {
-  const int t = blockIdx.y;
+  const int t = blockIdx.y;   // (part and ssq start at the first row's entry; T: rows of a slice of part)
   const int col = (blockIdx.x * 256 + threadIdx.x) * 8;
   unsigned long long key[8] = {0ull, 0ull, 0ull, 0ull, 0ull, 0ull, 0ull, 0ull};
   if (col < V) {   // V is a multiple of 16: a thread's 8 columns are all in range or all out
@@ -3300,25 +3300,30 @@ static hipError_t forward_t(const Model& m, const Work& w, const Step& s, Prof* 
     if (s.cap && (e = cap(l + 1, 0, w.xbuf, R16 * d * ESZ)) != hipSuccess) return e;
   }
   // LM head (without K slices when its reduction fits one workgroup), logits
-  // + chunk maxima, argmax
+  // + chunk maxima; argmax in run_accept.  The last `head` rows only, from the
+  // row tile that holds the first of them on.
+  const int head = s.head ? s.head : R, row0 = (R - head) / 16 * 16, hrows = R - row0;
+  const uint4* hx = w.xbuf + (size_t)(row0 / 16) * Sd * 64;
   const bool lm1 = lm_head_one_slice(d, DT);
   if ((e = timed(prof, PC_LMHEAD, st, [&] {
-         if (!lm1) return gemm<DT>(m.lm_head, w.xbuf, m.V, d, R, w.part, st);
+         if (!lm1) return gemm<DT>(m.lm_head, hx, m.V, d, hrows, w.part, st);
          EpArgs la{};
-         la.w = m.lm_head; la.x = w.xbuf; la.S = Sd; la.n_tiles = m.V / 16; la.n_items = m.V / 16; la.y = w.part;
-         return gemm_ep<DT, EP_STORE>(la, R, st);
+         la.w = m.lm_head; la.x = hx; la.S = Sd; la.n_tiles = m.V / 16; la.n_items = m.V / 16; la.y = w.part;
+         return gemm_ep<DT, EP_STORE>(la, hrows, st);
        })) != hipSuccess)
     return e;
   const int sk_lm = lm1 ? 1 : sk_d;
   const int nchunk = (m.V + 2047) / 2048;
   const bool topk = s.mode == 3;
   if ((e = timed(prof, PC_FINISH, st, [&] {
+         const float* part = w.part + (size_t)(R - head - row0) * m.V;
+         const float* ssq = w.ssq + (size_t)(R - head) * RES_MAX_PARTS;
          if (topk)
-           hipLaunchKernelGGL(logits_kernel<true>, dim3(nchunk, R), dim3(256), 0, st, w.part, sk_lm, R, m.V,
-                              w.logits, w.amax, nchunk, w.ssq, d, m.eps);
+           hipLaunchKernelGGL(logits_kernel<true>, dim3(nchunk, head), dim3(256), 0, st, part, sk_lm, hrows, m.V,
+                              w.logits, w.amax, nchunk, ssq, d, m.eps);
          else
-           hipLaunchKernelGGL(logits_kernel<false>, dim3(nchunk, R), dim3(256), 0, st, w.part, sk_lm, R, m.V,
-                              w.logits, w.amax, nchunk, w.ssq, d, m.eps);
+           hipLaunchKernelGGL(logits_kernel<false>, dim3(nchunk, head), dim3(256), 0, st, part, sk_lm, hrows, m.V,
+                              w.logits, w.amax, nchunk, ssq, d, m.eps);
          return last();
        })) != hipSuccess)
     return e;
@@ -3409,9 +3414,10 @@ hipError_t run_accept(const Model& m, const Work& w, const Step& s, Prof* prof, 
                          w.rowstat, gsum, w.result, w.host_result);
       return hipGetLastError();
     }
-    if (s.T > ACC_MAX_T) return hipErrorInvalidValue;
+    const int T = s.head ? s.head : s.T;   // (a prefill's decision needs its last rows only)
+    if (T > ACC_MAX_T) return hipErrorInvalidValue;
     hipLaunchKernelGGL(accept_kernel, dim3(s.B), dim3(ACC_THREADS), 0, st, w.amax, nchunk, w.tok, w.prow, w.greedy,
-                       w.verdict, s.T, s.mode, w.result, w.host_result, w.rec);
+                       w.verdict, T, s.mode, w.result, w.host_result, w.rec);
     return hipGetLastError();
   });
 }
