@@ -1113,10 +1113,129 @@ struct WideArgs {
   const float* rs;      // SWIGLU: row scales [R], or null: from the chunk sums
 };
 
+// Epilogue of the p-th pair of feature tiles (PAIRS: a rotary or gate/up pair;
+// otherwise tiles 2p and 2p + 1) for one row: v[0], v[1] = the two tiles'
+// products, features 4 grp .. + 3 of each.  Every lane of a wave enters.
+template <int DT, int EPI>
+__device__ __forceinline__ void wide_epilogue(const WideArgs& a, int row, int p, int grp, const f32x4 (&v)[2]) {
+  constexpr bool PAIRS = EPI == EP_ROPE || EPI == EP_SWIGLU;
+  const int R = a.e.R, n_tiles = a.e.n_tiles;
+  const bool rok = row < R;
+  if (PAIRS) {
+    if (p >= a.e.n_items) return;
+    const int hp = EPI == EP_ROPE ? a.e.hd / 32 : 1;
+    if (EPI == EP_SWIGLU) {
+      if (!rok) return;
+      const float rs = a.rs ? a.rs[row] : row_scale(a.e.ssq, row, a.e.d, a.e.eps);
+      float zv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) zv[q] = silu_mul(v[0][q] * rs, v[1][q] * rs);
+      const size_t fi = frag_index<DT>(row, 16 * p + 4 * grp, a.z_S);
+      if (DT == DT_BF16)
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.z) + fi) =
+            make_uint2(f2bf_bits(zv[0]) | (f2bf_bits(zv[1]) << 16), f2bf_bits(zv[2]) | (f2bf_bits(zv[3]) << 16));
+      else
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.z) + fi) = make_float4(zv[0], zv[1], zv[2], zv[3]);
+      return;
+    }
+    if (!rok) return;
+    const int head = p / hp, i0 = 16 * (p % hp) + 4 * grp, half = a.e.hd / 2;
+    const float rs = row_scale(a.e.ssq, row, a.e.d, a.e.eps);
+    float y1[4], y2[4];
+    if (head < a.e.H + a.e.Hkv) {
+      const auto cr = make_rsrc(a.e.rope, a.e.rope_bytes);
+      const unsigned co = (unsigned)(((size_t)a.e.pos[row] * half + i0) * 8);
+      const uint4 u0 = bload<0>(cr, co), u1 = bload<0>(cr, co + 16);
+      const float cs[8] = {__uint_as_float(u0.x), __uint_as_float(u0.y), __uint_as_float(u0.z), __uint_as_float(u0.w),
+                           __uint_as_float(u1.x), __uint_as_float(u1.y), __uint_as_float(u1.z), __uint_as_float(u1.w)};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float x1 = v[0][q] * rs, x2 = v[1][q] * rs;
+        y1[q] = fmaf(x1, cs[2 * q], -(x2 * cs[2 * q + 1]));   // (fixed contraction)
+        y2[q] = fmaf(x2, cs[2 * q], x1 * cs[2 * q + 1]);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        y1[q] = v[0][q] * rs;
+        y2[q] = v[1][q] * rs;
+      }
+    }
+    auto put4 = [&](void* base, size_t e, const float* y) {
+      if (DT == DT_BF16)
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(base) + e) =
+            make_uint2(f2bf_bits(y[0]) | (f2bf_bits(y[1]) << 16), f2bf_bits(y[2]) | (f2bf_bits(y[3]) << 16));
+      else
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(base) + e) = make_float4(y[0], y[1], y[2], y[3]);
+    };
+    if (head < a.e.H) {
+      const size_t qb = ((size_t)row * a.e.H + head) * a.e.hd;
+      put4(a.e.q, qb + i0, y1);
+      put4(a.e.q, qb + i0 + half, y2);
+      return;
+    }
+    const bool isv = head >= a.e.H + a.e.Hkv;
+    const int kh = head - a.e.H - (isv ? a.e.Hkv : 0);
+    if (a.e.kv_layer) {
+      const int slot = a.e.rowslot[row], page = slot >> 6, sp = slot & 63;
+      const size_t hb = (((size_t)page * 2 + (isv ? 1 : 0)) * a.e.Hkv + kh) * 64 * a.e.hd;
+      if (!isv) {
+        put4(a.e.kv_layer, hb + (size_t)sp * a.e.hd + i0, y1);
+        put4(a.e.kv_layer, hb + (size_t)sp * a.e.hd + i0 + half, y2);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          store_elt<DT>(a.e.kv_layer, hb + (size_t)(i0 + q) * 64 + sp, y1[q]);
+          store_elt<DT>(a.e.kv_layer, hb + (size_t)(i0 + q + half) * 64 + sp, y2[q]);
+        }
+      }
+    }
+    if (a.e.kv_cap) {   // test aid: the block's k rows, then its v rows, [R][Hkv][hd]
+      const size_t cb = ((isv ? (size_t)R * a.e.Hkv : 0) + (size_t)row * a.e.Hkv + kh) * a.e.hd;
+      put4(a.e.kv_cap, cb + i0, y1);
+      put4(a.e.kv_cap, cb + i0 + half, y2);
+    }
+    return;
+  }
+#pragma unroll
+  for (int h2 = 0; h2 < 2; ++h2) {
+    const int tile = 2 * p + h2, f = 16 * tile + 4 * grp;
+    if (tile >= n_tiles) break;
+    if (EPI == EP_STORE) {
+      if (rok)
+        *reinterpret_cast<float4*>(a.e.y + (size_t)row * (16 * n_tiles) + f) =
+            make_float4(v[h2][0], v[h2][1], v[h2][2], v[h2][3]);
+    } else if (EPI == EP_RESID) {
+      float4 hv = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (rok) hv = *reinterpret_cast<const float4*>(a.e.h + (size_t)row * a.e.d + f);
+      const float4 gv = *reinterpret_cast<const float4*>(a.e.gain + f);
+      const float ho[4] = {hv.x, hv.y, hv.z, hv.w}, gn[4] = {gv.x, gv.y, gv.z, gv.w};
+      float hn[4], xv[4], ss = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        hn[q] = ho[q] + v[h2][q];
+        ss = fmaf(hn[q], hn[q], ss);
+        xv[q] = hn[q] * gn[q];
+      }
+      ss += __shfl_xor(ss, 16);
+      ss += __shfl_xor(ss, 32);
+      if (rok) {
+        *reinterpret_cast<float4*>(a.e.h + (size_t)row * a.e.d + f) = make_float4(hn[0], hn[1], hn[2], hn[3]);
+        const size_t fi = frag_index<DT>(row, f, a.e.x_S);
+        if (DT == DT_BF16)
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.e.xout) + fi) =
+              make_uint2(f2bf_bits(xv[0]) | (f2bf_bits(xv[1]) << 16), f2bf_bits(xv[2]) | (f2bf_bits(xv[3]) << 16));
+        else
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.e.xout) + fi) = make_float4(xv[0], xv[1], xv[2], xv[3]);
+        if (grp == 0) a.e.ssqt[(size_t)row * n_tiles + tile] = ss;
+      }
+    }
+  }
+}
+
 template <int DT, int MT, int NT, int EPI, bool NTW>
 __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) {
   constexpr int W = GEMM_WAVES;
-  constexpr int ESZ = Geo<DT>::ESZ;
   constexpr bool PAIRS = EPI == EP_ROPE || EPI == EP_SWIGLU;
   static_assert(NT % 2 == 0 && MT <= W, "two feature tiles per reduction round, one wave per row tile");
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 15, grp = lane >> 4;
@@ -1189,123 +1308,6 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) 
     }
   };
 
-  // epilogue of row tile m = wave, reduction round r: v[0], v[1] = the two
-  // feature tiles' products for row row0 + c, features 4 grp .. + 3
-  auto epilogue = [&](int rg, int fg, int r, const f32x4 (&v)[2]) {
-    const int row = (rg * MT + wv) * 16 + c;
-    const bool rok = row < R;
-    if (PAIRS) {
-      const int p = fg * (NT / 2) + r;
-      if (p >= a.e.n_items) return;
-      if (EPI == EP_SWIGLU) {
-        if (!rok) return;
-        const float rs = a.rs ? a.rs[row] : row_scale(a.e.ssq, row, a.e.d, a.e.eps);
-        float zv[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) zv[q] = silu_mul(v[0][q] * rs, v[1][q] * rs);
-        const size_t fi = frag_index<DT>(row, 16 * p + 4 * grp, a.z_S);
-        if (DT == DT_BF16)
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.z) + fi) =
-              make_uint2(f2bf_bits(zv[0]) | (f2bf_bits(zv[1]) << 16), f2bf_bits(zv[2]) | (f2bf_bits(zv[3]) << 16));
-        else
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.z) + fi) = make_float4(zv[0], zv[1], zv[2], zv[3]);
-        return;
-      }
-      if (!rok) return;
-      const int head = p / hp, i0 = 16 * (p % hp) + 4 * grp, half = a.e.hd / 2;
-      const float rs = row_scale(a.e.ssq, row, a.e.d, a.e.eps);
-      float y1[4], y2[4];
-      if (head < a.e.H + a.e.Hkv) {
-        const auto cr = make_rsrc(a.e.rope, a.e.rope_bytes);
-        const unsigned co = (unsigned)(((size_t)a.e.pos[row] * half + i0) * 8);
-        const uint4 u0 = bload<0>(cr, co), u1 = bload<0>(cr, co + 16);
-        const float cs[8] = {__uint_as_float(u0.x), __uint_as_float(u0.y), __uint_as_float(u0.z), __uint_as_float(u0.w),
-                             __uint_as_float(u1.x), __uint_as_float(u1.y), __uint_as_float(u1.z), __uint_as_float(u1.w)};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float x1 = v[0][q] * rs, x2 = v[1][q] * rs;
-          y1[q] = fmaf(x1, cs[2 * q], -(x2 * cs[2 * q + 1]));   // (fixed contraction)
-          y2[q] = fmaf(x2, cs[2 * q], x1 * cs[2 * q + 1]);
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          y1[q] = v[0][q] * rs;
-          y2[q] = v[1][q] * rs;
-        }
-      }
-      auto put4 = [&](void* base, size_t e, const float* y) {
-        if (DT == DT_BF16)
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(base) + e) =
-              make_uint2(f2bf_bits(y[0]) | (f2bf_bits(y[1]) << 16), f2bf_bits(y[2]) | (f2bf_bits(y[3]) << 16));
-        else
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(base) + e) = make_float4(y[0], y[1], y[2], y[3]);
-      };
-      if (head < a.e.H) {
-        const size_t qb = ((size_t)row * a.e.H + head) * a.e.hd;
-        put4(a.e.q, qb + i0, y1);
-        put4(a.e.q, qb + i0 + half, y2);
-        return;
-      }
-      const bool isv = head >= a.e.H + a.e.Hkv;
-      const int kh = head - a.e.H - (isv ? a.e.Hkv : 0);
-      if (a.e.kv_layer) {
-        const int slot = a.e.rowslot[row], page = slot >> 6, sp = slot & 63;
-        const size_t hb = (((size_t)page * 2 + (isv ? 1 : 0)) * a.e.Hkv + kh) * 64 * a.e.hd;
-        if (!isv) {
-          put4(a.e.kv_layer, hb + (size_t)sp * a.e.hd + i0, y1);
-          put4(a.e.kv_layer, hb + (size_t)sp * a.e.hd + i0 + half, y2);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            store_elt<DT>(a.e.kv_layer, hb + (size_t)(i0 + q) * 64 + sp, y1[q]);
-            store_elt<DT>(a.e.kv_layer, hb + (size_t)(i0 + q + half) * 64 + sp, y2[q]);
-          }
-        }
-      }
-      if (a.e.kv_cap) {   // test aid: the block's k rows, then its v rows, [R][Hkv][hd]
-        const size_t cb = ((isv ? (size_t)R * a.e.Hkv : 0) + (size_t)row * a.e.Hkv + kh) * a.e.hd;
-        put4(a.e.kv_cap, cb + i0, y1);
-        put4(a.e.kv_cap, cb + i0 + half, y2);
-      }
-      return;
-    }
-#pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2) {
-      const int tile = fg * NT + 2 * r + h2, f = 16 * tile + 4 * grp;
-      if (tile >= n_tiles) break;
-      if (EPI == EP_STORE) {
-        if (rok)
-          *reinterpret_cast<float4*>(a.e.y + (size_t)row * (16 * n_tiles) + f) =
-              make_float4(v[h2][0], v[h2][1], v[h2][2], v[h2][3]);
-      } else if (EPI == EP_RESID) {
-        float4 hv = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (rok) hv = *reinterpret_cast<const float4*>(a.e.h + (size_t)row * a.e.d + f);
-        const float4 gv = *reinterpret_cast<const float4*>(a.e.gain + f);
-        const float ho[4] = {hv.x, hv.y, hv.z, hv.w}, gn[4] = {gv.x, gv.y, gv.z, gv.w};
-        float hn[4], xv[4], ss = 0.f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          hn[q] = ho[q] + v[h2][q];
-          ss = fmaf(hn[q], hn[q], ss);
-          xv[q] = hn[q] * gn[q];
-        }
-        ss += __shfl_xor(ss, 16);
-        ss += __shfl_xor(ss, 32);
-        if (rok) {
-          *reinterpret_cast<float4*>(a.e.h + (size_t)row * a.e.d + f) = make_float4(hn[0], hn[1], hn[2], hn[3]);
-          const size_t fi = frag_index<DT>(row, f, a.e.x_S);
-          if (DT == DT_BF16)
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.e.xout) + fi) =
-                make_uint2(f2bf_bits(xv[0]) | (f2bf_bits(xv[1]) << 16), f2bf_bits(xv[2]) | (f2bf_bits(xv[3]) << 16));
-          else
-            *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.e.xout) + fi) = make_float4(xv[0], xv[1], xv[2], xv[3]);
-          if (grp == 0) a.e.ssqt[(size_t)row * n_tiles + tile] = ss;
-        }
-      }
-    }
-  };
-
   // the task's chains are complete: add them in wave order, two feature tiles
   // at a time (wave m: row tile m), and run the epilogue
   auto reduce = [&]() {
@@ -1326,7 +1328,7 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) 
 #pragma unroll
           for (int j = 1; j < W; ++j) v[h2] += red[j][2 * wv + h2][lane];
         }
-        epilogue(rg, fg, r, v);
+        wide_epilogue<DT, EPI>(a, (rg * MT + wv) * 16 + c, fg * (NT / 2) + r, grp, v);
       }
       __syncthreads();
     }
@@ -1355,6 +1357,162 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) 
         if (C.task >= t1) return;
       }
     }
+  }
+}
+
+// Large gate/up projections and LM heads of bf16 models.  What bounds
+// gemm_wide_kernel is the rate at which a CU takes fragments in: 6 + 6 for 36
+// matrix instructions (513 rows at the 7B width: 0.6 PFLOP/s, about 20 bytes
+// per clock and CU).  Here a workgroup owns MT row tiles x 16 feature tiles, two
+// feature tiles per wave, and its waves run the eight chains of the reduction
+// one after another: `acc` holds the chain and `tot` the sum of the chains
+// before it, which is the sum of the kernels above bit for bit, and MT + 16
+// fragments serve 16 MT instructions.  The row tiles' fragments go through LDS,
+// four super-steps of a chain per barrier; the weights go straight to registers,
+// one such stage ahead.  Eight waves of 256 registers: with four waves of 512 a
+// matrix instruction with its sums in the accumulation registers took 26 clocks
+// instead of 19 (gate/up 138 us).  What bounds it now is LDS: every wave reads
+// all MT fragments, 975 clocks per super-step at MT = 7 against 448 for the
+// matrix instructions.  Gate/up 155 -> 121 us (7 row tiles) and LM head
+// 192 -> 171 us (6) at 513 rows of the 7B width, gate/up 44.5 -> 36.3 us at
+// 488 rows of the 1B width.
+constexpr int TILE_WAVES = 8, TILE_NT = 2;   // waves; feature tiles per wave
+constexpr int TILE_Q = 4;                    // super-steps per stage
+
+template <int MT, int EPI>
+__global__ __launch_bounds__(TILE_WAVES * 64, 2) void gemm_tile_kernel(WideArgs a) {
+  constexpr int TW = TILE_WAVES, NT = TILE_NT, Q = TILE_Q;
+  constexpr int XN = (MT * Q + TW - 1) / TW;   // row fragments a wave fetches per stage
+  static_assert(EPI == EP_SWIGLU || EPI == EP_STORE, "the projections with enough feature tiles");
+  static_assert(TW % Q == 0 && NT == 2, "TW / Q waves share a super-step's row fragments; a wave owns one pair");
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 15, grp = lane >> 4;
+  const int S = a.e.S, R = a.e.R, nrt = (R + 15) / 16, n_tiles = a.e.n_tiles;
+  const int spc = S / (GEMM_WAVES * Q);   // stages per chain
+  const auto xs = make_rsrc(a.e.x, (unsigned)((size_t)nrt * S * 1024));
+  const auto ws = make_rsrc(a.e.w, (unsigned)((size_t)n_tiles * S * 1024));
+  __shared__ uint4 xl[2][Q][MT][64];
+
+  // tasks to XCDs as in gemm_wide_kernel
+  const int per = (a.ntask + 7) / 8, t0 = (int)(blockIdx.x & 7) * per, t1 = min(a.ntask, t0 + per);
+  const int stride = gridDim.x >> 3, first = t0 + (int)(blockIdx.x >> 3);
+  if (first >= t1) return;
+  struct Pos {
+    int task, ch, j;   // task, chain, stage of the chain
+  };
+  Pos X{first, 0, 0}, Wp{first, 0, 0};
+  // moves to the next stage; true when that is another task's
+  auto next = [&](Pos& p) {
+    if (++p.j < spc) return false;
+    p.j = 0;
+    if (++p.ch < GEMM_WAVES) return false;
+    p.ch = 0;
+    p.task += stride;
+    return true;
+  };
+  int x0;            // first row tile of X's task
+  unsigned wo[NT];   // byte offsets of the feature tiles of Wp's task
+  auto x_task = [&](int task) { x0 = task % a.ng * MT; };
+  auto w_task = [&](int task) {
+    const int p = task / a.ng * TW + wv;   // the wave's pair of feature tiles
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int t = EPI == EP_SWIGLU ? min(p, a.e.n_items - 1) + n * a.e.n_items : min(NT * p + n, n_tiles - 1);
+      wo[n] = (unsigned)(t * S) * 1024u;
+    }
+  };
+  uint4 xr[XN], xf[2][MT], wq[Q][NT];
+  f32x4 acc[MT][NT], tot[MT][NT];
+
+  // requests this wave's super-step of the stage X (zeros past the last task)
+  auto load_x = [&]() {
+    const unsigned vo = X.task < t1 ? (unsigned)lane * 16u : OOB;
+    const unsigned so = (unsigned)(X.ch + GEMM_WAVES * (Q * X.j + wv % Q)) * 1024u;
+#pragma unroll
+    for (int i = 0; i < XN; ++i) {
+      const int t = min(x0 + wv / Q * XN + i, nrt - 1);
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(xs, vo, (unsigned)(t * S) * 1024u + so, 0);
+      xr[i] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+    if (next(X) && X.task < t1) x_task(X.task);
+  };
+  auto store_x = [&](int b) {
+#pragma unroll
+    for (int i = 0; i < XN; ++i)
+      if (wv / Q * XN + i < MT) xl[b][wv % Q][wv / Q * XN + i][lane] = xr[i];
+  };
+  // requests super-step q of the stage Wp
+  auto load_w = [&](int q) {
+    const unsigned vo = Wp.task < t1 ? (unsigned)lane * 16u : OOB;
+    const unsigned so = (unsigned)(Wp.ch + GEMM_WAVES * (Q * Wp.j + q)) * 1024u;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(ws, vo, wo[n] + so, 0);
+      wq[q][n] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+  };
+  auto next_w = [&]() {
+    if (next(Wp) && Wp.task < t1) w_task(Wp.task);
+  };
+
+  x_task(first);
+  w_task(first);
+  load_x();
+#pragma unroll
+  for (int q = 0; q < Q; ++q) load_w(q);
+  next_w();
+  store_x(0);
+  load_x();
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < MT; ++m) xf[0][m] = xl[0][0][m][lane];
+  int b = 0;
+  for (int task = first;;) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) tot[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int ch = 0; ch < GEMM_WAVES; ++ch) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < spc; ++j) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          // The next super-step's fragments are read before this one is multiplied.
+          // Buffer b ^ 1 is free at the stage's last super-step: its readers passed
+          // the barrier of the stage before.
+          if (q == Q - 1) {
+            store_x(b ^ 1);
+            load_x();
+            __syncthreads();
+          }
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+            xf[(q + 1) & 1][m] = q == Q - 1 ? xl[b ^ 1][0][m][lane] : xl[b][(q + 1) % Q][m][lane];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m][n] = mma<DT_BF16>(wq[q][n], xf[q & 1][m], acc[m][n]);
+          __builtin_amdgcn_sched_barrier(0);
+          load_w(q);
+        }
+        next_w();
+        b ^= 1;
+      }
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) tot[m][n] += acc[m][n];
+    }
+    const int fg = task / a.ng, rg = task - fg * a.ng;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const f32x4 v[2] = {tot[m][0], tot[m][1]};
+      wide_epilogue<DT_BF16, EPI>(a, (rg * MT + m) * 16 + c, fg * TW + wv, grp, v);
+    }
+    if ((task += stride) >= t1) return;
   }
 }
 
@@ -1404,10 +1562,22 @@ static void launch_wide(const WideArgs& a, int mt, int nt, dim3 grid, hipStream_
   else hipLaunchKernelGGL((gemm_wide_kernel<DT, 7, 4, EPI, NTW>), grid, block, 0, st, a);
 }
 
+template <int MT, int EPI>
+static hipError_t launch_tile(WideArgs a, int nrt, int cols, hipStream_t st) {
+  a.ng = (nrt + MT - 1) / MT;
+  a.ntask = a.ng * ((cols + TILE_WAVES * TILE_NT - 1) / (TILE_WAVES * TILE_NT));
+  const dim3 grid(std::min(256, (a.ntask + 7) / 8 * 8));
+  hipLaunchKernelGGL((gemm_tile_kernel<MT, EPI>), grid, dim3(TILE_WAVES * 64), 0, st, a);
+  return hipGetLastError();
+}
+
 // The projection of `a` for R rows on gemm_wide_kernel.  The tile is the one
 // with the least estimated time: rounds of 256 workgroups, each of which takes
 // in MT + NT fragments per super-step and pays about one fragment's worth of
-// fixed time.
+// fixed time (2.0 us per such unit at 128 super-steps).  On the same scale a
+// round of gemm_tile_kernel takes 4 MT + 2 (60 us at MT = 7, 48-57 at 6); it
+// needs whole stages in every chain.  At 257 rows of the 7B width that leaves
+// gate/up here (85 us against 99), at 130 rows too (59, 64; LM head 73, 65).
 template <int DT, int EPI>
 static hipError_t gemm_wide(WideArgs a, int R, hipStream_t st) {
   static const int tiles[][2] = {{5, 2}, {5, 4}, {4, 6}, {5, 6}, {6, 6}, {7, 4}};
@@ -1420,6 +1590,12 @@ static hipError_t gemm_wide(WideArgs a, int R, hipStream_t st) {
     const int c = (n + 255) / 256 * (mt + nt + 1);
     if (c < cost) { cost = c; best = i; }
   }
+  if constexpr (DT == DT_BF16 && (EPI == EP_SWIGLU || EPI == EP_STORE))
+    if (a.e.S % (GEMM_WAVES * TILE_Q) == 0) {
+      const int fgs = (cols + TILE_WAVES * TILE_NT - 1) / (TILE_WAVES * TILE_NT);
+      const int c6 = ((nrt + 5) / 6 * fgs + 255) / 256 * 26, c7 = ((nrt + 6) / 7 * fgs + 255) / 256 * 30;
+      if (std::min(c6, c7) < cost) return c7 < c6 ? launch_tile<7, EPI>(a, nrt, cols, st) : launch_tile<6, EPI>(a, nrt, cols, st);
+    }
   const int mt = tiles[best][0], nt = tiles[best][1];
   a.ng = (nrt + mt - 1) / mt;
   a.ntask = a.ng * ((cols + nt - 1) / nt);
