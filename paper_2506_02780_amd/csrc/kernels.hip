@@ -1322,7 +1322,9 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) 
   auto load = [&](uint4 (&xf)[MT], uint4 (&wf)[NT]) {
     const int sl = wv + W * L.i;
     const unsigned vo = (L.task < t1 && sl < S) ? (unsigned)lane * 16u : OOB;
-    const unsigned so = (unsigned)sl * 1024u;
+    // (a masked load's scalar offset stays inside the buffer too: the range
+    // check subtracts it from the size, and the difference must not wrap)
+    const unsigned so = (unsigned)min(sl, S - 1) * 1024u;
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(ws, vo, wo[n] + so, NTW ? 2 : 0);

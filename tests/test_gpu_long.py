@@ -234,6 +234,11 @@ def _models():
     # vocabulary tiles on six at 513 rows, neither a multiple of a workgroup's eight pairs
     yield "bf16 d1024", _bf16_small(d_model=1024, n_heads=8, n_kv_heads=2, ffn=6464, vocab=16416), 0.04
     yield "bf16 d2048", _bf16_small(d_model=2048, n_heads=16, n_kv_heads=4, ffn=1120, vocab=2080), 0.03
+    # reductions that are no multiple of the eight waves: 17 super-steps in gate/up (whose row scales are chunk sums:
+    # d is no multiple of 256) and the LM head; 12 in the O projection, in bf16 and fp32
+    yield "bf16 d544", _bf16_small(d_model=544, n_heads=6, n_kv_heads=2, head_dim=64, ffn=1120, vocab=2080), 0.05
+    yield "bf16 q384", _bf16_small(d_model=512, n_heads=6, n_kv_heads=2, head_dim=64, ffn=1120, vocab=2080), 0.05
+    yield "f32 q192", get_shape("tiny", n_heads=3, n_kv_heads=1, ffn=688), 0.1
     yield "bf16 d4096", _bf16_small(d_model=4096, n_heads=32, n_kv_heads=8, ffn=1120, vocab=2080), 0.02
 
 
