@@ -222,7 +222,7 @@ struct GemmArgs {
 inline int gemm_slices(int S) {
   int sk = 1;
   while (S > GEMM_SPW * GEMM_WAVES * sk) sk *= 2;
-  return sk;   // <= 16 for every K the library accepts (K <= 32768)
+  return sk;   // K <= 32768: at most 16 (bf16) or 32 (fp32); over d_model (<= 8192): at most 4 or 8
 }
 
 // Workgroup (row group rg, tile group g, slice k) = blockIdx rg * P + g * SK + k
@@ -382,21 +382,20 @@ static hipError_t gemm(const uint4* w, const uint4* x, int N, int K, int R, floa
   return launch_gemm<DT, false>(a, mt, dim3(rg * a.P), st);
 }
 
-constexpr int MAX_SLICES = 16;   // gemm_slices() never exceeds this for K <= 32768
-
-// Sums of the slice partials of elements (t, n .. n + 7) and, where n2 >= 0,
+// Sums of the slice partials of elements (t, n .. n + 7) and, where TWO,
 // (t, n2 .. n2 + 7), in slice order.  The slice count (a power of two) is a
 // constant in each branch, so that every load is issued before the first add
 // (with a run-time count each group of four elements was a round trip of its
 // own).  Bound by the partials, read once: 33B batch of 260 rows 856.7 -> 828.0
 // us, K = 512 step over four 7B layers 1789 -> 1759, K = 32 459.2 -> 455.5.
-template <int SK, bool TWO>
+// (K0 > 0: slices K0 .. K0 + SK - 1 added to what v and v2 hold.)
+template <int SK, bool TWO, int K0 = 0>
 __device__ __forceinline__ void sum_slices_n(const float* __restrict__ part, int T, int N, int t, int n, int n2,
                                              float (&v)[8], float (&v2)[8]) {
   float4 u[TWO ? 4 : 2][SK];
 #pragma unroll
   for (int k = 0; k < SK; ++k) {
-    const float* r = part + ((size_t)k * T + t) * N;
+    const float* r = part + ((size_t)(K0 + k) * T + t) * N;
     u[0][k] = *reinterpret_cast<const float4*>(r + n);
     u[1][k] = *reinterpret_cast<const float4*>(r + n + 4);
     if constexpr (TWO) {
@@ -406,13 +405,17 @@ __device__ __forceinline__ void sum_slices_n(const float* __restrict__ part, int
   }
 #pragma unroll
   for (int i = 0; i < (TWO ? 4 : 2); ++i) {
+    float(&o)[8] = i < 2 ? v : v2;
+    const int e = 4 * (i & 1);
     float4 w = u[i][0];
+    if (K0) { w.x = o[e] + w.x; w.y = o[e + 1] + w.y; w.z = o[e + 2] + w.z; w.w = o[e + 3] + w.w; }
 #pragma unroll
     for (int k = 1; k < SK; ++k) { w.x += u[i][k].x; w.y += u[i][k].y; w.z += u[i][k].z; w.w += u[i][k].w; }
-    float(&o)[8] = i < 2 ? v : v2;
-    o[4 * (i & 1)] = w.x; o[4 * (i & 1) + 1] = w.y; o[4 * (i & 1) + 2] = w.z; o[4 * (i & 1) + 3] = w.w;
+    o[e] = w.x; o[e + 1] = w.y; o[e + 2] = w.z; o[e + 3] = w.w;
   }
 }
+// (reductions over d_model, the only ones that are read in pairs, have at most 8 slices)
+constexpr int MAX_D_SLICES = 8;
 template <bool TWO>
 __device__ __forceinline__ void sum_slices(const float* __restrict__ part, int SK, int T, int N, int t, int n, int n2,
                                            float (&v)[8], float (&v2)[8]) {
@@ -420,10 +423,13 @@ __device__ __forceinline__ void sum_slices(const float* __restrict__ part, int S
     case 1: sum_slices_n<1, TWO>(part, T, N, t, n, n2, v, v2); break;
     case 2: sum_slices_n<2, TWO>(part, T, N, t, n, n2, v, v2); break;
     case 4: sum_slices_n<4, TWO>(part, T, N, t, n, n2, v, v2); break;
-    case 8: sum_slices_n<8, TWO>(part, T, N, t, n, n2, v, v2); break;
-    default:   // (in two halves: 64 loads would not fit the registers)
-      sum_slices_n<MAX_SLICES, false>(part, T, N, t, n, 0, v, v);
-      if (TWO) sum_slices_n<MAX_SLICES, false>(part, T, N, t, n2, 0, v2, v2);
+    case MAX_D_SLICES: sum_slices_n<MAX_D_SLICES, TWO>(part, T, N, t, n, n2, v, v2); break;
+    default:
+      if constexpr (!TWO) {
+        sum_slices_n<16, false>(part, T, N, t, n, n2, v, v2);
+        // (fp32 over more than 16384 columns; 64 loads at once would not fit the registers)
+        if (SK == 32) sum_slices_n<16, false, 16>(part, T, N, t, n, n2, v, v2);
+      }
   }
 }
 __device__ __forceinline__ void sum_slices8(const float* __restrict__ part, int SK, int T, int N, int t, int n,
@@ -1789,16 +1795,16 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict
   if (p >= pairs) return;
   const int head = p / half, i = p % half;       // head over [q heads | k heads | v heads]
   const int f1 = head * hd + i, f2 = f1 + half;
-  float p1[MAX_SLICES], p2[MAX_SLICES];
+  float p1[MAX_D_SLICES], p2[MAX_D_SLICES];
 #pragma unroll
-  for (int k = 0; k < MAX_SLICES; ++k)
+  for (int k = 0; k < MAX_D_SLICES; ++k)
     if (k < SK) {
       p1[k] = part[((size_t)k * T + t) * N + f1];
       p2[k] = part[((size_t)k * T + t) * N + f2];
     }
   float x1 = p1[0], x2 = p2[0];
 #pragma unroll
-  for (int k = 1; k < MAX_SLICES; ++k)
+  for (int k = 1; k < MAX_D_SLICES; ++k)
     if (k < SK) { x1 += p1[k]; x2 += p2[k]; }
   const float rs = row_scale(ssq, t, d, eps);   // the input norm's row scale
   x1 *= rs;

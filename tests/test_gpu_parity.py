@@ -64,6 +64,29 @@ def test_tiny_fp32_planted_drafts_accept_exactly(ee, std):
     eng.close()
 
 
+@pytest.mark.parametrize("heads,kv,ffn", [(260, 20, 688), (4, 4, 16400), (4, 4, 32768), (4, 4, 16384)])
+def test_fp32_reductions_of_up_to_32_slices_match_oracle(ee, heads, kv, ffn):
+    """fp32 reductions over more than 16384 columns (the O projection of 260
+    heads, ragged and full down projections) are cut into 32 slices, all of
+    which enter the sum; 16384 columns have 16.  Tolerance: a product's longest
+    chain of dependent additions is about 100 (64 in a slice's chain, 8 chains,
+    32 slices), 2^-24 each, in two norms and three products: below 1e-5 of the
+    logits' norm (a missing slice is of order 0.1)."""
+    shape = get_shape("tiny", n_layers=1, n_heads=heads, n_kv_heads=kv, ffn=ffn)
+    w = gen_weights(shape, seed=78, std=0.05)
+    prompt = zipf_tokens(shape.vocab, 40, seed=6)
+    ref = OracleSession(shape, w)
+    eng = ee.Engine(shape, w, max_ctx=128, k_max=8)
+    ref.prefill(prompt)
+    eng.prefill(0, prompt)
+    eng.rollback(0, 40, ref.pending)
+    ref.verify(zipf_tokens(shape.vocab, 8, seed=7))
+    eng.verify(0, zipf_tokens(shape.vocab, 8, seed=7))
+    err = np.linalg.norm(eng.logits() - ref.last_logits) / np.linalg.norm(ref.last_logits)
+    assert err <= 1e-5, err
+    eng.close()
+
+
 def test_bf16_gqa_session_matches_oracle(ee):
     """Six Reuse steps of K = 32 (GQA, random gains); every step compared,
     near ties decided the GPU's way followed by the oracle (G12)."""
