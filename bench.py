@@ -464,6 +464,24 @@ def get_shape_for_table():
     return get_shape("7b")
 
 
+def _blocks(names):
+    """(first, last) indices of the blocks that end in an acceptance (and, for
+    trees, the compaction after it): from the staging kernel on.  A commit-only
+    block has no such end (the next block's staging closes it) and a stochastic
+    one ends in its draw; neither is listed."""
+    out, first = [], None
+    for i, n in enumerate(names):
+        if n.startswith("stage_"):
+            first = i
+        elif n == "resample_kernel":
+            first = None
+        elif n == "accept_kernel" and first is not None:
+            tree = i + 1 < len(names) and names[i + 1].startswith("compact_kernel")
+            out.append((first, i + 1 if tree else i))
+            first = None
+    return out
+
+
 def rocprof_summary(d: str):
     """Markdown tables from rocprofv3 CSV output under directory d: kernel
     statistics, per-role durations of T = 33 layers, the kernel-gap fraction
@@ -500,18 +518,10 @@ def rocprof_summary(d: str):
                 tot += st.median(v)
                 print(f"| {role} | `{names[starts[0] + j]}` | {len(v)} | {st.median(v):.2f} | {st.mean(v):.2f} |")
         print(f"| one layer (sum of medians) | | | {tot:.2f} | |")
-        # blocks of 33 rows: stage_in_kernel or stage_embed_kernel .. accept_kernel; kernels busy
-        # = the union of their intervals
+        # blocks of 33 rows; kernels busy = the union of their intervals
         spans, busy = [], []
-        i = 0
-        while i < len(names):
-            if not names[i].startswith("stage_"):
-                i += 1
-                continue
-            j = i
-            while j < len(names) and names[j] != "accept_kernel":
-                j += 1
-            if j < len(names) and any(names[x] == "resid_kernel<1, 1>" and gy[x] == 33 for x in range(i, j)):
+        for i, j in _blocks(names):
+            if any(names[x] == "resid_kernel<1, 1>" and gy[x] == 33 for x in range(i, j)):
                 b, cur_end = 0, t0[i]
                 for x in range(i, j + 1):
                     s0, s1 = max(t0[x], cur_end), t1[x]
@@ -520,7 +530,6 @@ def rocprof_summary(d: str):
                         cur_end = s1
                 spans.append((t1[j] - t0[i]) / 1e3)
                 busy.append(b / 1e3)
-            i = j + 1
         if spans:
             fr = [1 - b / s for b, s in zip(busy, spans)]
             print(f"\nT = 33 blocks: {len(spans)}; first kernel start to last kernel end: median "

@@ -28,6 +28,19 @@ def test_layer_detection_follows_the_fused_layer():
     assert bench._layer_starts(names[:5]) == []
 
 
+def test_blocks_of_a_trace_do_not_run_into_each_other():
+    layer = [p for _, p in bench.LAYER_ROLES]
+    commit = ["stage_in_kernel", "resid_kernel<1, 0>"] + layer
+    greedy = ["stage_embed_kernel<1>"] + layer + ["logits_kernel<false>", "accept_kernel"]
+    sampled = ["stage_embed_kernel<1>"] + layer + ["sample_accept_kernel", "resample_sums_kernel", "resample_kernel"]
+    tree = greedy + ["compact_kernel<1, 128>"]
+    other = ["__amd_rocclr_copyBuffer"]
+    names = commit + greedy + sampled + other + greedy + tree + commit
+    a, b = len(commit), len(commit + greedy + sampled + other)
+    c = b + len(greedy)
+    assert bench._blocks(names) == [(a, a + len(greedy) - 1), (b, b + len(greedy) - 1), (c, c + len(tree) - 1)]
+
+
 def test_committed_profile_readers_match_the_source_or_report_nothing():
     # each returns the committed figure while its source hash matches, else None
     t = bench.measured_traffic()
