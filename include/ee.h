@@ -382,6 +382,7 @@ int32_t ee_use_graphs(ee_ctx* ctx, int32_t on);
 /* Kernel classes of one forward, for ee_profile. */
 enum {
   EE_PROF_NORM = 0,     /* embedding / residual add + RMSNorm launches  */
+                        /* (short blocks: with the staging of the inputs) */
   EE_PROF_QKV = 1,      /* QKV GEMM                                     */
   EE_PROF_ATTN = 2,     /* split attention over the paged KV cache      */
   EE_PROF_COMBINE = 3,  /* merge of the attention splits                */

@@ -395,7 +395,7 @@ ee::StageCopy stage_ranges(const ee_ctx* c, const ee::Step& step) {
 // with the results out (+ tree compaction).
 hipError_t launch_block(ee_ctx* c, const ee::Step& step, ee::Prof* prof, const ee::Work& w) {
   hipError_t e;
-  if ((e = ee::run_stage_in(c->m, w, step, stage_ranges(c, step), c->st)) != hipSuccess) return e;
+  if ((e = ee::run_stage_in(c->m, w, step, stage_ranges(c, step), prof, c->st)) != hipSuccess) return e;
   if ((e = ee::run_forward(c->m, w, step, prof, c->st)) != hipSuccess) return e;
   if (step.mode == 5) return hipSuccess;
   if ((e = ee::run_accept(c->m, w, step, prof, c->st)) != hipSuccess) return e;

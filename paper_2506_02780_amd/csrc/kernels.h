@@ -152,7 +152,7 @@ struct StageCopy {
   int off[10], len[10];     // word offset and word count of each range
   int total;                // sum of the word counts
 };
-hipError_t run_stage_in(const Model& m, const Work& w, const Step& s, const StageCopy& sc, hipStream_t st);
+hipError_t run_stage_in(const Model& m, const Work& w, const Step& s, const StageCopy& sc, Prof* prof, hipStream_t st);
 
 hipError_t run_forward(const Model& m, const Work& w, const Step& s, Prof* prof, hipStream_t st);
 hipError_t run_accept(const Model& m, const Work& w, const Step& s, Prof* prof, hipStream_t st);

@@ -3589,21 +3589,24 @@ __global__ __launch_bounds__(RES_THREADS) void stage_embed_kernel(StageCopy sc, 
   }
 }
 
-hipError_t run_stage_in(const Model& m, const Work& w, const Step& s, const StageCopy& sc, hipStream_t st) {
+hipError_t run_stage_in(const Model& m, const Work& w, const Step& s, const StageCopy& sc, Prof* prof,
+                        hipStream_t st) {
   if (sc.total <= 0) return hipSuccess;
   const int R = s.T * s.B;
   if (stage_embeds(m.d, R)) {
     const int nx = (m.d + RES_COLS - 1) / RES_COLS;
     const dim3 grid(nx * R + (sc.total + RES_THREADS - 1) / RES_THREADS);
-    if (m.dt == DT_BF16)
-      hipLaunchKernelGGL(stage_embed_kernel<DT_BF16>, grid, dim3(RES_THREADS), 0, st, sc, m.embed, w.h,
-                         m.layers[0].attn_gain, m.d, (void*)w.xbuf, m.d / ks_of(m.dt), w.ssq, nx, R);
-    else
-      hipLaunchKernelGGL(stage_embed_kernel<DT_F32>, grid, dim3(RES_THREADS), 0, st, sc, m.embed, w.h,
-                         m.layers[0].attn_gain, m.d, (void*)w.xbuf, m.d / ks_of(m.dt), w.ssq, nx, R);
-  } else {
-    hipLaunchKernelGGL(stage_in_kernel, dim3((sc.total + 255) / 256), dim3(256), 0, st, sc);
+    return timed(prof, PC_NORM, st, [&] {   // (the block's embedding launch)
+      if (m.dt == DT_BF16)
+        hipLaunchKernelGGL(stage_embed_kernel<DT_BF16>, grid, dim3(RES_THREADS), 0, st, sc, m.embed, w.h,
+                           m.layers[0].attn_gain, m.d, (void*)w.xbuf, m.d / ks_of(m.dt), w.ssq, nx, R);
+      else
+        hipLaunchKernelGGL(stage_embed_kernel<DT_F32>, grid, dim3(RES_THREADS), 0, st, sc, m.embed, w.h,
+                           m.layers[0].attn_gain, m.d, (void*)w.xbuf, m.d / ks_of(m.dt), w.ssq, nx, R);
+      return hipGetLastError();
+    });
   }
+  hipLaunchKernelGGL(stage_in_kernel, dim3((sc.total + 255) / 256), dim3(256), 0, st, sc);
   return hipGetLastError();
 }
 

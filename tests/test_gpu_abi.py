@@ -138,3 +138,19 @@ def test_time_gemm_on_rows_nothing_has_staged(ee, fill):
     for cls in ("qkv", "oproj", "gateup", "down", "lmhead"):
         assert e.time_gemm(cls, 65, 1) > 0.0
     e.close()
+
+
+@pytest.mark.parametrize("K", [0, 8, 200])
+def test_profile_counts_the_embedding_and_every_norm_whatever_the_block(ee, K):
+    # one embedding launch per block (short blocks form it with the staging of their inputs) and one residual add
+    # + norm per layer after the down projection; the FFN-side norm is in the O projection's epilogue
+    shape = get_shape("tiny")
+    e = ee.Engine(shape, gen_weights(shape, seed=9, std=0.1), max_ctx=512, max_seqs=1, k_max=256)
+    e.prefill(0, zipf_tokens(shape.vocab, 20, seed=3))
+    e.profile(["norm", "qkv"])
+    e.profile_read(reset=True)
+    for _ in range(2):
+        e.verify(0, zipf_tokens(shape.vocab, K, seed=4))
+    n = {c: v[1] for c, v in e.profile_read().items()}
+    assert n["norm"] == 2 * (1 + shape.n_layers) and n["qkv"] == 2 * shape.n_layers
+    e.close()
