@@ -730,20 +730,85 @@ static void launch_gemm_swiglu(const FkArgs& a, int spw, dim3 grid, hipStream_t 
   }
 }
 
-// Whether a block of R rows runs a one-slice projection of S super-steps as
-// gemm_wide_kernel: from three 32-row groups on (66 rows).  Measured inside
-// 7B steps (S = 128; us per launch, 32-row groups -> wide): at 513 rows
-// gate/up 221 -> 152, QKV 80 -> 54, O 53 -> 45, LM head 321 -> 189; at 96 rows
-// 52.5 -> 44, 25 -> 23, 16.7 -> 16, 78 -> 58.  At 65 rows two groups still
-// stream cold weights near the HBM rate: the K = 64 step takes 560 us with the
-// group kernels and 565-577 with QKV and the LM head wide.  At the 1B width
-// (S = 64) a task's fixed cost weighs more: launched back to back, the LM head
-// takes 32 -> 24 us at 65 rows and QKV 10.4 -> 9.6 at 66, but O 7.2 -> 8.0 and
-// gate/up 21.2 -> 21.7 at 129 (10.4 -> 8.1 and 34 -> 32 at 257), so these two
-// change over at 193.  Results do not depend on the choice.
-inline bool wide_block(int R, int S, int epi) {
-  if (S > 64 || epi == EP_ROPE || epi == EP_STORE) return R > 2 * FK_GROUP + 1;
-  return R > 192;
+// The tile of a wide block (R rows x `cols` feature tiles, S super-steps): MT row
+// tiles x NT feature tiles of gemm_wide_kernel, or (tile) MT row tiles of
+// gemm_tile_kernel.  The one with the least estimated time: rounds of 256
+// workgroups, each of which takes in MT + NT fragments per super-step and pays
+// about one fragment's worth of fixed time (2.0 us per such unit at 128
+// super-steps).  On the same scale a round of gemm_tile_kernel takes 4 MT + 2
+// (60 us at MT = 7, 48-57 at 6); it needs whole stages in every chain.  At 257
+// rows of the 7B width that leaves gate/up on gemm_wide_kernel (85 us against
+// 99), at 130 rows too (59, 64; LM head 73, 65).
+constexpr int TILE_WAVES = 8, TILE_NT = 2;   // gemm_tile_kernel: waves; feature tiles per wave
+constexpr int TILE_Q = 4;                    // and super-steps per stage
+struct WidePlan {
+  int mt, nt;    // row tiles, feature tiles of a task
+  int rounds;    // tasks of the busiest workgroup
+  int in;        // fragments that workgroup takes in per super-step, over its rounds
+  bool tile;
+};
+template <int DT>
+inline WidePlan wide_plan(int R, int cols, int S, int epi) {
+  static const int tiles[][2] = {{5, 2}, {5, 4}, {4, 6}, {5, 6}, {6, 6}, {7, 4}};
+  const int nrt = (R + 15) / 16;
+  WidePlan p{};
+  int cost = INT32_MAX;
+  for (const auto& t : tiles) {
+    const int mt = t[0], nt = t[1];
+    const int rounds = (((nrt + mt - 1) / mt) * ((cols + nt - 1) / nt) + 255) / 256;
+    if (rounds * (mt + nt + 1) < cost) {
+      cost = rounds * (mt + nt + 1);
+      p = WidePlan{mt, nt, rounds, rounds * (mt + nt), false};
+    }
+  }
+  if (DT == DT_BF16 && (epi == EP_SWIGLU || epi == EP_STORE) && S % (GEMM_WAVES * TILE_Q) == 0)
+    for (int mt = 6; mt <= 7; ++mt) {
+      const int nt = TILE_WAVES * TILE_NT, rounds = (((nrt + mt - 1) / mt) * ((cols + nt - 1) / nt) + 255) / 256;
+      if (rounds * (4 * mt + 2) < cost) {
+        cost = rounds * (4 * mt + 2);
+        p = WidePlan{mt, nt, rounds, rounds * (4 * mt + 1), true};
+      }
+    }
+  return p;
+}
+
+// Workgroups per row group of the kernels that hold 32-row groups, with several groups.
+inline int fk_group_wgs(int ng) { return std::max(8, 256 / ng / 8 * 8); }
+
+// Whether a block of R rows runs a one-slice projection of S super-steps and
+// n_items outputs (tiles, or pairs of them) on the wide kernels rather than in
+// 32-row groups: from three groups on (66 rows; O and gate/up of S <= 64: 193),
+// where it moves less.  Results do not depend on the choice.
+//   bf16: fragments the busiest workgroup takes in.  A group's workgroup takes
+// the tiles of its items (for the super-steps its instance has, a power of two
+// per wave) and its rows once, which with the fixed costs is worth 3 fragments
+// in O, 5 in QKV (rotary, rows of K and V), 6 in the LM head and 1 in gate/up
+// (a wide block forms its row scales in a launch of its own); one row group,
+// which fills fewer workgroups, 1 less.  Measured inside steps of 8 widths from
+// 256 to 4096 at 66 to 513 rows, where the two differ (us per launch, groups ->
+// wide): 7B width, 513 rows, gate/up 212 -> 119, QKV 66 -> 41, O 42 -> 33, LM
+// head 302 -> 169; 66 rows, QKV 22.5 -> 18.7 but O 15.6 -> 18.9; 97 rows, gate/up
+// 50.6 -> 56.8; d = 1536, 66 rows, QKV 7.0 -> 8.7; d = 512, 257 rows, O 3.7 -> 5.1.
+// (At 65 rows two groups still stream cold weights near the HBM rate: the 7B K =
+// 64 step over four layers takes 560 us with the groups, 565-577 with QKV and the
+// LM head wide.)
+//   fp32: products, which bound both.  A group's item takes 3.5 per tile (two
+// row tiles and the 33rd row's, with its fixed cost), a wide task MT x NT.  d =
+// 256, 257 rows (24 workgroups wide): O 3.9 -> 6.2 us, gate/up 7.6 -> 8.1; 400
+// rows, gate/up 9.9 -> 8.2, QKV 8.0 -> 6.1; d = 2048, 513 rows, gate/up 279 -> 215,
+// 161 rows, QKV 34 -> 42.
+template <int DT>
+inline bool wide_block(int R, int S, int n_items, int epi) {
+  if (R <= (S > 64 || epi == EP_ROPE || epi == EP_STORE ? 2 * FK_GROUP + 1 : 192)) return false;
+  const int per = epi == EP_ROPE || epi == EP_SWIGLU ? 2 : 1;
+  const WidePlan p = wide_plan<DT>(R, per * n_items, S, epi);
+  const int P = fk_group_wgs(fk_groups(R)), tiles = (n_items + P - 1) / P * per;
+  int Sg = GEMM_WAVES;
+  while (Sg < S) Sg *= 2;
+  if (DT == DT_F32) return 2 * p.rounds * p.mt * p.nt * S <= 7 * tiles * Sg - (epi == EP_SWIGLU ? 8 * S : 0);
+  const int fixed = epi == EP_ROPE ? 5 : epi == EP_RESID ? 3 : epi == EP_STORE ? 6 : 1;
+  const bool one = !p.tile && (R + 15) / 16 <= p.mt;
+  return p.in * S <= tiles * Sg + (fixed - one) * S;
 }
 template <int DT>
 static hipError_t gemm_swiglu_wide(const uint4* wgu, const uint4* x, int F, int d, int R, void* z, float* ssq,
@@ -756,7 +821,8 @@ static hipError_t gemm_swiglu_wide(const uint4* wgu, const uint4* x, int F, int 
 template <int DT>
 static hipError_t gemm_swiglu(const uint4* wgu, const uint4* x, int F, int d, int R, void* z, float* ssq,
                               const float* ssqt, float eps, hipStream_t st) {
-  if (wide_block(R, d / Geo<DT>::KS, EP_SWIGLU)) return gemm_swiglu_wide<DT>(wgu, x, F, d, R, z, ssq, ssqt, eps, st);
+  if (wide_block<DT>(R, d / Geo<DT>::KS, F / 16, EP_SWIGLU))
+    return gemm_swiglu_wide<DT>(wgu, x, F, d, R, z, ssq, ssqt, eps, st);
   FkArgs a;
   a.w = wgu; a.x = x; a.z = z;
   a.ssq = ssq; a.ssqt = ssqt; a.d = d; a.eps = eps;
@@ -772,7 +838,7 @@ static hipError_t gemm_swiglu(const uint4* wgu, const uint4* x, int F, int d, in
   // one row group: as many workgroups as give each the same count of pairs
   // (688 pairs: 230 x 3, not 176 x 3 + 80 x 2)
   const int per_wg = (a.n_pairs + 255) / 256;
-  a.P = ng == 1 ? std::max(1, (a.n_pairs + per_wg - 1) / per_wg) : std::max(8, 256 / ng / 8 * 8);
+  a.P = ng == 1 ? std::max(1, (a.n_pairs + per_wg - 1) / per_wg) : fk_group_wgs(ng);
   const dim3 grid(ng * a.P);
   if (ssqt) {
     if (R <= 16) launch_gemm_swiglu<DT, 1, true>(a, spw, grid, st);
@@ -1416,9 +1482,6 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) 
 // matrix instructions.  Gate/up 155 -> 121 us (7 row tiles) and LM head
 // 192 -> 171 us (6) at 513 rows of the 7B width, gate/up 44.5 -> 36.3 us at
 // 488 rows of the 1B width.
-constexpr int TILE_WAVES = 8, TILE_NT = 2;   // waves; feature tiles per wave
-constexpr int TILE_Q = 4;                    // super-steps per stage
-
 template <int MT, int EPI>
 __global__ __launch_bounds__(TILE_WAVES * 64, 2) void gemm_tile_kernel(WideArgs a) {
   constexpr int TW = TILE_WAVES, NT = TILE_NT, Q = TILE_Q;
@@ -1602,46 +1665,23 @@ static void launch_wide(const WideArgs& a, int mt, int nt, dim3 grid, hipStream_
   else hipLaunchKernelGGL((gemm_wide_kernel<DT, 7, 4, EPI, NTW>), grid, block, 0, st, a);
 }
 
-template <int MT, int EPI>
-static hipError_t launch_tile(WideArgs a, int nrt, int cols, hipStream_t st) {
-  a.ng = (nrt + MT - 1) / MT;
-  a.ntask = a.ng * ((cols + TILE_WAVES * TILE_NT - 1) / (TILE_WAVES * TILE_NT));
-  const dim3 grid(std::min(256, (a.ntask + 7) / 8 * 8));
-  hipLaunchKernelGGL((gemm_tile_kernel<MT, EPI>), grid, dim3(TILE_WAVES * 64), 0, st, a);
-  return hipGetLastError();
-}
-
-// The projection of `a` for R rows on gemm_wide_kernel.  The tile is the one
-// with the least estimated time: rounds of 256 workgroups, each of which takes
-// in MT + NT fragments per super-step and pays about one fragment's worth of
-// fixed time (2.0 us per such unit at 128 super-steps).  On the same scale a
-// round of gemm_tile_kernel takes 4 MT + 2 (60 us at MT = 7, 48-57 at 6); it
-// needs whole stages in every chain.  At 257 rows of the 7B width that leaves
-// gate/up here (85 us against 99), at 130 rows too (59, 64; LM head 73, 65).
+// The projection of `a` for R rows on the wide kernels (wide_plan).
 template <int DT, int EPI>
 static hipError_t gemm_wide(WideArgs a, int R, hipStream_t st) {
-  static const int tiles[][2] = {{5, 2}, {5, 4}, {4, 6}, {5, 6}, {6, 6}, {7, 4}};
   a.e.R = R;
   const int nrt = (R + 15) / 16, cols = a.e.n_items * (EPI == EP_ROPE || EPI == EP_SWIGLU ? 2 : 1);
-  int best = 0, cost = INT32_MAX;
-  for (int i = 0; i < 6; ++i) {
-    const int mt = tiles[i][0], nt = tiles[i][1];
-    const int n = ((nrt + mt - 1) / mt) * ((cols + nt - 1) / nt);
-    const int c = (n + 255) / 256 * (mt + nt + 1);
-    if (c < cost) { cost = c; best = i; }
-  }
-  if constexpr (DT == DT_BF16 && (EPI == EP_SWIGLU || EPI == EP_STORE))
-    if (a.e.S % (GEMM_WAVES * TILE_Q) == 0) {
-      const int fgs = (cols + TILE_WAVES * TILE_NT - 1) / (TILE_WAVES * TILE_NT);
-      const int c6 = ((nrt + 5) / 6 * fgs + 255) / 256 * 26, c7 = ((nrt + 6) / 7 * fgs + 255) / 256 * 30;
-      if (std::min(c6, c7) < cost) return c7 < c6 ? launch_tile<7, EPI>(a, nrt, cols, st) : launch_tile<6, EPI>(a, nrt, cols, st);
-    }
-  const int mt = tiles[best][0], nt = tiles[best][1];
-  a.ng = (nrt + mt - 1) / mt;
-  a.ntask = a.ng * ((cols + nt - 1) / nt);
+  const WidePlan p = wide_plan<DT>(R, cols, a.e.S, EPI);
+  a.ng = (nrt + p.mt - 1) / p.mt;
+  a.ntask = a.ng * ((cols + p.nt - 1) / p.nt);
   const dim3 grid(std::min(256, (a.ntask + 7) / 8 * 8));
-  if (a.ng == 1) launch_wide<DT, EPI, true>(a, mt, nt, grid, st);
-  else launch_wide<DT, EPI, false>(a, mt, nt, grid, st);
+  if constexpr (DT == DT_BF16 && (EPI == EP_SWIGLU || EPI == EP_STORE))
+    if (p.tile) {
+      if (p.mt == 7) hipLaunchKernelGGL((gemm_tile_kernel<7, EPI>), grid, dim3(TILE_WAVES * 64), 0, st, a);
+      else hipLaunchKernelGGL((gemm_tile_kernel<6, EPI>), grid, dim3(TILE_WAVES * 64), 0, st, a);
+      return hipGetLastError();
+    }
+  if (a.ng == 1) launch_wide<DT, EPI, true>(a, p.mt, p.nt, grid, st);
+  else launch_wide<DT, EPI, false>(a, p.mt, p.nt, grid, st);
   return hipGetLastError();
 }
 
@@ -1669,7 +1709,7 @@ template <int DT, int EPI>
 static hipError_t gemm_ep(EpArgs a, int R, hipStream_t st) {
   if (a.S > FK_MAX_S) return hipErrorInvalidValue;
   if (EPI == EP_ROPE && (a.hd % 32 || a.n_tiles % (a.hd / 16))) return hipErrorInvalidValue;
-  if (wide_block(R, a.S, EPI)) {
+  if (wide_block<DT>(R, a.S, a.n_items, EPI)) {
     WideArgs w{};
     w.e = a;
     return gemm_wide<DT, EPI>(w, R, st);
@@ -1678,7 +1718,7 @@ static hipError_t gemm_ep(EpArgs a, int R, hipStream_t st) {
   int spw = 1;
   while (spw * GEMM_WAVES < a.S) spw *= 2;
   const int ng = fk_groups(R);
-  a.P = ng == 1 ? std::max(1, std::min(256, a.n_items)) : std::max(8, 256 / ng / 8 * 8);
+  a.P = ng == 1 ? std::max(1, std::min(256, a.n_items)) : fk_group_wgs(ng);
   const dim3 grid(ng * a.P);
   if (R <= 16) launch_gemm_ep<DT, 1, EPI>(a, spw, grid, st);
   else launch_gemm_ep<DT, 2, EPI>(a, spw, grid, st);
