@@ -188,7 +188,8 @@ int32_t ee_verify_noalloc(ee_ctx* ctx, int32_t seq, const int32_t* draft_tokens,
  * its own: every result equals that of ee_verify on the sequence alone.
  * Either every sequence advances or, on error, none does.  Errors: as
  * ee_verify, plus EE_EINVAL for n_seq outside [1, max_seqs] or a sequence
- * listed twice. */
+ * listed twice, EE_ECAPACITY where the block's GEMM slice partials would
+ * reach 2 GiB. */
 int32_t ee_verify_batch(ee_ctx* ctx, int32_t n_seq, const int32_t* seqs, const int32_t* drafts,
                         int32_t K, const int32_t* parents, int32_t* accept_lens,
                         int32_t* next_tokens, int32_t* accepted_nodes);

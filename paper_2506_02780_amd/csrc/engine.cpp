@@ -622,6 +622,9 @@ int verify_many(ee_ctx* c, int n_seq, const int32_t* seqs, const int32_t* drafts
   if (K < 0 || K > c->cfg.k_max) return fail(c, EE_EINVAL, "K outside [0, k_max]");
   const int T = K + 1;
   if (parents && K > MAX_TREE) return fail(c, EE_EINVAL, "draft trees have at most 64 nodes");
+  // (valid_cfg bounds the slices of d_model and ffn; those of n_heads * head_dim can be more)
+  if (partial_cols(c->cfg) * (size_t)n_seq * T * 4 >= (size_t(1) << 31))
+    return fail(c, EE_ECAPACITY, "the GEMM partials of this block would reach 2 GiB (fewer sequences or draft tokens)");
   std::vector<int> depth((size_t)n_seq * (MAX_TREE + 1));
   std::vector<Seq*> ss(n_seq);
   for (int b = 0; b < n_seq; ++b) {

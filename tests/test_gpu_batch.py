@@ -168,3 +168,35 @@ def test_batch_errors_leave_every_sequence_unchanged(ee):
     res = eng.verify_batch([1, 0], [d[0][:5], d[1][:5]])  # fits, in either order
     assert [eng.seq_state(b)[0] for b in range(2)] == [before[0][0] + 1 + res[1][0], before[1][0] + 1 + res[0][0]]
     eng.close()
+
+
+def test_batch_whose_partials_reach_2_gib_is_refused(ee):
+    """The O projection over 257 heads in fp32 has 32 slices, d_model 8: a
+    batch of 2079 rows would have partials past 2 GiB, which the kernels' 32-bit
+    offsets do not reach; it is refused and leaves every sequence as it was,
+    and a smaller batch of the same engine runs."""
+    shape = get_shape("tiny", n_layers=1, d_model=8192, n_heads=257, n_kv_heads=1, head_dim=64, ffn=32, vocab=32)
+    s = shape
+
+    class Zeros:
+        embed = lm_head = np.zeros((s.vocab, s.d_model), np.float32)
+        final_gain = np.ones(s.d_model, np.float32)
+
+        def layer(self, l):
+            z = lambda r, c: np.zeros((r, c), np.float32)
+            return dict(wq=z(s.q_dim, s.d_model), wk=z(s.kv_dim, s.d_model), wv=z(s.kv_dim, s.d_model),
+                        wo=z(s.d_model, s.q_dim), w_gate=z(s.ffn, s.d_model), w_up=z(s.ffn, s.d_model),
+                        w_down=z(s.d_model, s.ffn), attn_gain=self.final_gain, ffn_gain=self.final_gain)
+
+    n = 33
+    eng = ee.Engine(shape, Zeros(), max_ctx=128, max_seqs=n, k_max=62)
+    for b in range(n):
+        eng.prefill(b, [1])
+    before = [eng.seq_state(b) for b in range(n)]
+    drafts = [np.zeros(62, np.int32)] * n
+    with pytest.raises(ee.EEError) as e:
+        eng.verify_batch(list(range(n)), drafts)
+    assert e.value.code == ee.EE_ECAPACITY
+    assert [eng.seq_state(b) for b in range(n)] == before
+    assert len(eng.verify_batch([0, 1], [d[:0] for d in drafts[:2]])) == 2
+    eng.close()
