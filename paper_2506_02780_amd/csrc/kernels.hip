@@ -1811,8 +1811,11 @@ __global__ __launch_bounds__(RES_THREADS) void resid_kernel(const void* __restri
 
 // Whether the kernel that stages a block's inputs also forms its first residual
 // update (stage_embed_kernel): few enough workgroups that each can read its
-// token over the host link (7B over four layers, K = 0 and 32: 394.5 -> 392.1
-// and 462.3 -> 459.5 us per step).
+// token over the host link.  Measured per step at d = 256, 2048, 4096 and 7168:
+// 0.3-3.5 us less from one workgroup to the bound (one point of 35, 0.4 more; 7B
+// over four layers, K = 0 and 32: 394.5 -> 392.1 and 462.3 -> 459.5).  Up to
+// 2052 workgroups the one launch was 0.2-6 us faster as well: the bound is on
+// the safe side.
 inline bool stage_embeds(int d, int R) { return R * ((d + RES_COLS - 1) / RES_COLS) <= 160; }
 
 // q/k/v of row t from the QKV partials: rotary on q and k (pairs (i, i+hd/2)
