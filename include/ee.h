@@ -90,7 +90,14 @@ typedef struct {
 } ee_weights;
 
 /* Sizes of the three caller allocations (bytes, 256-byte aligned pieces).
- * Return 0 for an invalid config. */
+ * Return 0 for an invalid config.
+ * The workspace is sized for blocks of max(max_seqs * (k_max + 1), P) rows,
+ * P = up to 512 rows of a prompt or extension (ee_prefill) whatever k_max is.
+ * Its largest part is the greater of the attention split states,
+ * (ceil(max_ctx / 256) + 1) * n_heads * rows * (head_dim + 2) * 4 bytes, and
+ * the GEMM slice partials, which share one place: 7B-class bf16, k_max 32, one
+ * sequence: 128 MB at max_ctx 2048, 322 MB at 8192 (1B class 166 MB, 33B class
+ * 558 MB at 8192). */
 size_t ee_packed_weight_bytes(const ee_model_config* cfg);
 size_t ee_kv_pool_bytes(const ee_model_config* cfg);
 size_t ee_workspace_bytes(const ee_model_config* cfg);
@@ -377,7 +384,9 @@ int32_t ee_capture(ee_ctx* ctx, void* dev_buf, size_t bytes);
  * the attention splits of the longest context, ceil((n + T) / 256)) are
  * captured once into a HIP graph and replayed (at most 512 shapes are kept;
  * past that the cache starts over); on == 0: every kernel is launched
- * individually.  Both run the same kernels with the same arguments. */
+ * individually.  Both run the same kernels with the same arguments.  (Prompts
+ * and extensions of more than k_max + 1 rows are always launched individually:
+ * their blocks' row counts follow their length.) */
 int32_t ee_use_graphs(ee_ctx* ctx, int32_t on);
 
 /* Kernel classes of one forward, for ee_profile. */

@@ -202,10 +202,13 @@ Layout make_layout(const ee_model_config* c) {
   L.ssqt = o; o += up(Rall * (d / 16) * 4);
   L.zbuf = o; o += up(Tpad * F * esz);
   L.q = o; o += up(Rall * H * hd * esz);
-  L.part = o; o += up((size_t)L.max_splits * Hkv * Rall * L.G * (hd + 2) * 4);
-  // split-K partials of the largest GEMM: [slices][rows][N] (the LM head of a
-  // prompt block: its last rows from the start of their row tile)
-  L.gpart = o; o += up(std::max(partial_cols(*c) * std::max(L.Rmax, L.Tmax + 15), partial_cols(*c, false) * Rall) * 4);
+  // attention split states, and in the same place the split-K partials of the
+  // largest GEMM, [slices][rows][N] (the LM head of a prompt block: its last
+  // rows from the start of their row tile): each is consumed by the launch
+  // after the one that writes it, so the two are never live together
+  L.part = L.gpart = o;
+  o += up(std::max((size_t)L.max_splits * Hkv * Rall * L.G * (hd + 2) * 4,
+                   std::max(partial_cols(*c) * std::max(L.Rmax, L.Tmax + 15), partial_cols(*c, false) * Rall) * 4));
   L.logits = o; o += up(L.Rmax * V * 4);
   L.amax = o; o += up(L.Rmax * ((V + 2047) / 2048) * 8 * 8);
   L.greedy = o; o += up(L.Rmax * 4);

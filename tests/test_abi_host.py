@@ -31,6 +31,32 @@ def test_every_declared_symbol_is_exported():
         assert hasattr(ee._lib, n), n
 
 
+@pytest.mark.parametrize("model,max_ctx,seqs,k_max", [("7b", 8192, 1, 32), ("7b", 2048, 1, 0), ("1b", 8192, 1, 32),
+                                                      ("33b", 8192, 1, 32), ("33b", 4096, 4, 64), ("tiny", 256, 1, 8)])
+def test_workspace_holds_one_of_attention_states_and_partials(model, max_ctx, seqs, k_max):
+    """Rows: the verify blocks' or a prompt block's (up to 512).  Attention split
+    states and GEMM partials share one place; the rest is a few values per row
+    and column, the verify blocks' logits and the rotary table."""
+    import paper_2506_02780_amd as ee
+    s = get_shape(model)
+    esz, verify = (2 if s.dtype == "bf16" else 4), seqs * (k_max + 1)
+    rows = max(verify, min(512, -(-max_ctx // 16) * 16))
+    states = (-(-max_ctx // 256) + 1) * s.n_heads * rows * (s.head_dim + 2) * 4
+
+    def slices(k):
+        n = 1
+        while k // (32 if esz == 2 else 16) > 64 * n:
+            n *= 2
+        return n
+    cols = max(slices(s.d_model) * (s.q_dim + 2 * s.kv_dim), slices(s.q_dim) * s.d_model,
+               slices(s.d_model) * 2 * s.ffn, slices(s.ffn) * s.d_model)
+    partials = 4 * max(cols * rows, slices(s.d_model) * s.vocab * max(verify, k_max + 16))
+    others = rows * (4 * s.d_model + s.d_model // 4 + esz * (2 * max(s.d_model, s.q_dim) + s.q_dim + s.ffn) + 64)
+    others += verify * (4 * s.vocab + s.vocab // 32 + 128) + max_ctx * s.head_dim * 4
+    total = ee.ee_workspace_bytes(ctypes.byref(ee.make_config(s, max_ctx=max_ctx, max_seqs=seqs, k_max=k_max)))
+    assert max(states, partials) < total < max(states, partials) + others + (1 << 16)
+
+
 def test_config_sizes_and_validation():
     import paper_2506_02780_amd as ee
     cfg = ee.make_config(get_shape("7b"), max_ctx=2048 + 65, k_max=64)
