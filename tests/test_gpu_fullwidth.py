@@ -195,9 +195,10 @@ def test_7b_layer_entropy_topk_over_2048_positions(ee):
 
 @pytest.mark.parametrize("k", [128, 512])
 def test_7b_layer_long_draft_over_2048_positions(ee, k):
-    """Long Reuse drafts at the 7B width: the fused projections in 32-row
-    groups (5 and 16 of them), the down projection and LM head in 80-row
-    groups, the wide attention kernel (33 and 129 query tiles)."""
+    """Long Reuse drafts at the 7B width: QKV and O on tiles of both operands,
+    the LM head (and gate/up at 513 rows) on the eight-wave tiles, the down
+    projection in two groups of five and five of seven row tiles, the wide
+    attention kernel (33 and 129 query tiles)."""
     _single(ee, "7b", 31, 2048, k, seed=60 + k)
 
 
