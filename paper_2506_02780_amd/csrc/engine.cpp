@@ -144,8 +144,8 @@ size_t partial_cols(const ee_model_config& g, bool lm_head = true) {
 
 // Rows of the blocks of prompts and extensions: up to 512 whatever
 // k_max is, since a block streams every weight once for all of its rows (1B,
-// 1000 tokens, k_max 64: 14.25 ms in 65-row blocks, 5.0 ms in blocks of 512,
-// 463 and 25 rows), halved until the block's attention states, GEMM
+// 1000 tokens, k_max 64: 15.7 ms in 65-row blocks, 3.8 ms in blocks of 512
+// and 488 rows), halved until the block's attention states, GEMM
 // partials and query columns stay within the bounds that valid_cfg sets for
 // verify blocks; at least k_max + 1.
 int prompt_rows(const ee_model_config& g) {
@@ -575,7 +575,7 @@ void stage_draft(ee_ctx* c, int b, int T, const Seq& s, const int32_t* draft, co
 // rows left over by whole blocks of k_max + 1 (at least one): the `tail`.  The
 // rows run in blocks of up to Pmax; the blocks before the last stop once their
 // keys and values are in the cache (no final layer past its QKV projection, no
-// LM head: 312 us per 513-row block at the 7B width), and the last one, which
+// LM head: 171 us per 513-row block at the 7B width), and the last one, which
 // holds the whole tail, runs the LM head for the tail only.  A row's arithmetic
 // does not depend on its block.  (A rounding-site capture records whole blocks
 // of at most k_max + 1 rows.)  On failure the sequence is left as it was.

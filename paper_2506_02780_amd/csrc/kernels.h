@@ -58,9 +58,10 @@ struct Model {
 
 // Per-step device buffers (all inside the caller's workspace).  A block holds
 // B sequences of T rows each, R = B * T rows in all (row b*T + t is row t of
-// sequence b); Rmax = max_seqs * (k_max + 1), or the rows of the largest
-// commit-only block (mode 5) where that is more, for the buffers up to `part`
-// and the staged tok, pos, prow and slot.
+// sequence b); Rmax = max_seqs * (k_max + 1), or the rows of the largest block
+// of a prompt or extension (modes 5 and 0, the latter with logits of its last
+// `head` rows only) where that is more, for the buffers up to `part` and the
+// staged tok, pos, prow and slot.
 struct Work {
   float* h;                 // [Rmax, d] residual stream
   float* ssq;               // [Rmax, 8] sums of h^2 over 1024-column chunks (the norms' row scales)

@@ -1468,8 +1468,8 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) 
 
 // Large gate/up projections and LM heads of bf16 models.  What bounds
 // gemm_wide_kernel is the rate at which a CU takes fragments in: 6 + 6 for 36
-// matrix instructions (513 rows at the 7B width: 0.6 PFLOP/s, about 20 bytes
-// per clock and CU).  Here a workgroup owns MT row tiles x 16 feature tiles, two
+// matrix instructions (513 rows at the 7B width: 0.6 PFLOP/s; QKV and O take in
+// 22 bytes per clock and CU, read from the L2 request counter).  Here a workgroup owns MT row tiles x 16 feature tiles, two
 // feature tiles per wave, and its waves run the eight chains of the reduction
 // one after another: `acc` holds the chain and `tot` the sum of the chains
 // before it, which is the sum of the kernels above bit for bit, and MT + 16
@@ -1477,11 +1477,14 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) 
 // four super-steps of a chain per barrier; the weights go straight to registers,
 // one such stage ahead.  Eight waves of 256 registers: with four waves of 512 a
 // matrix instruction with its sums in the accumulation registers took 26 clocks
-// instead of 19 (gate/up 138 us).  What bounds it now is LDS: every wave reads
-// all MT fragments, 975 clocks per super-step at MT = 7 against 448 for the
-// matrix instructions.  Gate/up 155 -> 121 us (7 row tiles) and LM head
-// 192 -> 171 us (6) at 513 rows of the 7B width, gate/up 44.5 -> 36.3 us at
-// 488 rows of the 1B width.
+// instead of 19 (gate/up 138 us).  It takes in 22 bytes per clock and CU like
+// gemm_wide_kernel, with twice the products per byte; its matrix cores are busy
+// 0.40 of the clocks and LDS, from which every wave reads all MT fragments,
+// 0.25 (counters at 513 rows of the 7B width, gate/up and LM head alike), so
+// intake and the waits of two waves per SIMD bound it, not LDS.  (MT = 7 with
+// SWIGLU takes all 256 registers and spills one.)  Gate/up 155 -> 121 us (7 row
+// tiles) and LM head 192 -> 171 us (6) at 513 rows of the 7B width, gate/up
+// 44.5 -> 36.3 us at 488 rows of the 1B width.
 template <int MT, int EPI>
 __global__ __launch_bounds__(TILE_WAVES * 64, 2) void gemm_tile_kernel(WideArgs a) {
   constexpr int TW = TILE_WAVES, NT = TILE_NT, Q = TILE_Q;
@@ -2757,7 +2760,9 @@ constexpr int MAX_SPLITS = 32;   // committed + block positions <= 8192
 // Merge the splits of every (row, head) in split order; write the attention
 // output as packed activations of the O projection.  4 dims per thread.  The
 // state of every split of the attention grid (max_splits, fixed at launch) is
-// fetched in one batch; only the first info[1] of the row's sequence take part.
+// fetched in one batch; only the first info[1] of the row's sequence take part
+// (a count that the compiled kernel requests once the batch has arrived: a
+// second round trip).
 constexpr int CMB_THREADS = 128;   // 4 (row, head) columns per workgroup at head_dim 128
 
 template <int DT, int HD>
