@@ -202,13 +202,20 @@ Layout make_layout(const ee_model_config* c) {
   L.ssqt = o; o += up(Rall * (d / 16) * 4);
   L.zbuf = o; o += up(Tpad * F * esz);
   L.q = o; o += up(Rall * H * hd * esz);
-  // attention split states, and in the same place the split-K partials of the
-  // largest GEMM, [slices][rows][N] (the LM head of a prompt block: its last
-  // rows from the start of their row tile): each is consumed by the launch
-  // after the one that writes it, so the two are never live together
-  L.part = L.gpart = o;
-  o += up(std::max((size_t)L.max_splits * Hkv * Rall * L.G * (hd + 2) * 4,
-                   std::max(partial_cols(*c) * std::max(L.Rmax, L.Tmax + 15), partial_cols(*c, false) * Rall) * 4));
+  // attention split states and the split-K partials of the largest GEMM,
+  // [slices][rows][N] (the LM head of a prompt block: its last rows from the
+  // start of their row tile), share one region: each is consumed by the launch
+  // after the one that writes it, so the two are never live together.  The
+  // smaller ends where the larger does, so that the blocks of ordinary drafts,
+  // which use the front of each, still find them apart (on the same bytes the
+  // attention kernel took 12.8 us instead of 11.6: 7B, K = 32).
+  const size_t states = up((size_t)L.max_splits * Hkv * Rall * L.G * (hd + 2) * 4);
+  const size_t partials =
+      up(std::max(partial_cols(*c) * std::max(L.Rmax, L.Tmax + 15), partial_cols(*c, false) * Rall) * 4);
+  const size_t region = std::max(states, partials);
+  L.part = o + region - states;
+  L.gpart = o + region - partials;
+  o += region;
   L.logits = o; o += up(L.Rmax * V * 4);
   L.amax = o; o += up(L.Rmax * ((V + 2047) / 2048) * 8 * 8);
   L.greedy = o; o += up(L.Rmax * 4);
