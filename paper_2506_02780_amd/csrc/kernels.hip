@@ -363,7 +363,7 @@ static hipError_t launch_gemm(const GemmArgs& a, int mt, dim3 grid, hipStream_t 
 // (narrow models leave CUs idle), the shortest such groups of three row tiles or
 // more.  Down projection, 97 rows, as one group of seven row tiles -> now: fp32
 // d = 512 9.99 -> 5.36 us, bf16 d = 1024 6.15 -> 4.30 (groups of five: 9.06, 5.40);
-// at d = 2048 and more the choice is that of the fewest groups.  A row's
+// the 1B, 7B and 33B shapes keep the fewest groups.  A row's
 // arithmetic is the same either way (and the same as in a launch of its own).
 template <int DT>
 static hipError_t gemm(const uint4* w, const uint4* x, int N, int K, int R, float* part,
