@@ -1668,15 +1668,25 @@ __global__ __launch_bounds__(64) void tile_scale_kernel(const float* __restrict_
   if (row < R && ch == 0) rs[row] = 1.0f / sqrtf(t / (float)d + eps);
 }
 
+// (One row group, NTW: of five row tiles or more, from 66 rows on; in O, whose
+// tiles are at most 256, always 5 x 2.)
 template <int DT, int EPI, bool NTW>
-static void launch_wide(const WideArgs& a, int mt, int nt, dim3 grid, hipStream_t st) {
+static hipError_t launch_wide(const WideArgs& a, int mt, int nt, dim3 grid, hipStream_t st) {
   const dim3 block(GEMM_WAVES * 64);
-  if (mt == 5 && nt == 2) hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 2, EPI, NTW>), grid, block, 0, st, a);
-  else if (mt == 5 && nt == 4) hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 4, EPI, NTW>), grid, block, 0, st, a);
-  else if (mt == 5) hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 6, EPI, NTW>), grid, block, 0, st, a);
-  else if (mt == 4) hipLaunchKernelGGL((gemm_wide_kernel<DT, 4, 6, EPI, NTW>), grid, block, 0, st, a);
-  else if (mt == 6) hipLaunchKernelGGL((gemm_wide_kernel<DT, 6, 6, EPI, NTW>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((gemm_wide_kernel<DT, 7, 4, EPI, NTW>), grid, block, 0, st, a);
+  if (mt == 5 && nt == 2) {
+    hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 2, EPI, NTW>), grid, block, 0, st, a);
+    return hipGetLastError();
+  }
+  if constexpr (!(NTW && EPI == EP_RESID)) {
+    if (mt == 5 && nt == 4) hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 4, EPI, NTW>), grid, block, 0, st, a);
+    else if (mt == 5 && nt == 6) hipLaunchKernelGGL((gemm_wide_kernel<DT, 5, 6, EPI, NTW>), grid, block, 0, st, a);
+    else if (mt == 6 && nt == 6) hipLaunchKernelGGL((gemm_wide_kernel<DT, 6, 6, EPI, NTW>), grid, block, 0, st, a);
+    else if (mt == 7 && nt == 4) hipLaunchKernelGGL((gemm_wide_kernel<DT, 7, 4, EPI, NTW>), grid, block, 0, st, a);
+    else if constexpr (!NTW) hipLaunchKernelGGL((gemm_wide_kernel<DT, 4, 6, EPI, NTW>), grid, block, 0, st, a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 
 // The projection of `a` for R rows on the wide kernels (wide_plan).
@@ -1694,9 +1704,8 @@ static hipError_t gemm_wide(WideArgs a, int R, hipStream_t st) {
       else hipLaunchKernelGGL((gemm_tile_kernel<6, EPI>), grid, dim3(TILE_WAVES * 64), 0, st, a);
       return hipGetLastError();
     }
-  if (a.ng == 1) launch_wide<DT, EPI, true>(a, p.mt, p.nt, grid, st);
-  else launch_wide<DT, EPI, false>(a, p.mt, p.nt, grid, st);
-  return hipGetLastError();
+  return a.ng == 1 ? launch_wide<DT, EPI, true>(a, p.mt, p.nt, grid, st)
+                   : launch_wide<DT, EPI, false>(a, p.mt, p.nt, grid, st);
 }
 
 // gemm_swiglu for wide blocks; the row scales of tile sums go to `ssq` first.
