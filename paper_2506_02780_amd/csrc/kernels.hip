@@ -788,26 +788,28 @@ inline int fk_group_wgs(int ng) { return std::max(8, 256 / ng / 8 * 8); }
 
 // Whether a block of R rows runs a one-slice projection of S super-steps and
 // n_items outputs (tiles, or pairs of them) on the wide kernels rather than in
-// 32-row groups: from three groups on (66 rows; O and gate/up of S <= 64: 193),
-// where it moves less.  Results do not depend on the choice.
+// 32-row groups: where it moves less, from three groups on (66 rows; O and
+// gate/up of S <= 64 from 193: below, 1B's gate/up loses 1.9 us at 97 rows and
+// gains 2.8 at 130).  Results do not depend on the choice.
 //   bf16: fragments the busiest workgroup takes in.  A group's workgroup takes
 // the tiles of its items (for the super-steps its instance has, a power of two
 // per wave) and its rows once, which with the fixed costs is worth 3 fragments
 // in O, 5 in QKV (rotary, rows of K and V), 6 in the LM head and 1 in gate/up
 // (a wide block forms its row scales in a launch of its own); one row group,
-// which fills fewer workgroups, 1 less.  Measured inside steps of 8 widths from
-// 256 to 4096 at 66 to 513 rows, where the two differ (us per launch, groups ->
-// wide): 7B width, 513 rows, gate/up 212 -> 119, QKV 66 -> 41, O 42 -> 33, LM
-// head 302 -> 169; 66 rows, QKV 22.5 -> 18.7 but O 15.6 -> 18.9; 97 rows, gate/up
-// 50.6 -> 56.8; d = 1536, 66 rows, QKV 7.0 -> 8.7; d = 512, 257 rows, O 3.7 -> 5.1.
-// (At 65 rows two groups still stream cold weights near the HBM rate: the 7B K =
-// 64 step over four layers takes 560 us with the groups, 565-577 with QKV and the
-// LM head wide.)
+// which fills fewer workgroups, 1 less.
 //   fp32: products, which bound both.  A group's item takes 3.5 per tile (two
-// row tiles and the 33rd row's, with its fixed cost), a wide task MT x NT.  d =
-// 256, 257 rows (24 workgroups wide): O 3.9 -> 6.2 us, gate/up 7.6 -> 8.1; 400
-// rows, gate/up 9.9 -> 8.2, QKV 8.0 -> 6.1; d = 2048, 513 rows, gate/up 279 -> 215,
-// 161 rows, QKV 34 -> 42.
+// row tiles and the 33rd row's, with its fixed cost), a wide task MT x NT.
+//   Measured inside whole steps, one projection at a time on either kernel, at
+// nine bf16 widths (256 to 4096) and four fp32 ones (256 to 2048), 66 to 513
+// rows; us per launch that the wide kernel saves: 7B width, 513 rows, gate/up 92,
+// QKV 25, O 9, LM head 133; 66 rows, QKV 3.8 but O -3.3; 97 rows, gate/up -6.2;
+// d = 1536, 66 rows, QKV -1.8; d = 512, 257 rows, O -1.3; fp32 d = 256, 193 rows
+// (24 workgroups), O -2.6; 400 rows, QKV 3.6, gate/up 1.7, O -1.8; d = 2048, 513
+// rows, gate/up 64; 161 rows, QKV -8.4.  The rule takes the slower kernel for 72
+// of the 8900 us between the two at these 588 points (by rows alone: 226).  (At 65
+// rows two groups still stream cold weights near the HBM rate: the 7B K = 64 step
+// over four layers takes 560 us with the groups, 565-577 with QKV and the LM head
+// wide.)
 template <int DT>
 inline bool wide_block(int R, int S, int n_items, int epi) {
   if (R <= (S > 64 || epi == EP_ROPE || epi == EP_STORE ? 2 * FK_GROUP + 1 : 192)) return false;
