@@ -360,10 +360,11 @@ static hipError_t launch_gemm(const GemmArgs& a, int mt, dim3 grid, hipStream_t 
 // group: one workgroup per CU, each streaming its weight tiles once.  More:
 // they share each weight stream through L2.  As few groups as the registers
 // allow, or where a workgroup's weight tiles are no more with shorter groups
-// (narrow models leave CUs idle), the shortest such groups of three row tiles or
-// more.  Down projection, 97 rows, as one group of seven row tiles -> now: fp32
-// d = 512 9.99 -> 5.36 us, bf16 d = 1024 6.15 -> 4.30 (groups of five: 9.06, 5.40);
-// the 1B, 7B and 33B shapes keep the fewest groups.  A row's
+// and every workgroup still has a CU (narrow models leave CUs idle), the shortest
+// such groups of three row tiles or more.  Down projection, 97 rows, as one
+// group of seven row tiles -> now: fp32 d = 512 9.99 -> 5.36 us, bf16 d = 1024
+// 6.15 -> 4.30 (groups of five: 9.06, 5.40); the 1B, 7B and 33B shapes keep the
+// fewest groups up to 513 rows.  A row's
 // arithmetic is the same either way (and the same as in a launch of its own).
 template <int DT>
 static hipError_t gemm(const uint4* w, const uint4* x, int N, int K, int R, float* part,
@@ -380,7 +381,8 @@ static hipError_t gemm(const uint4* w, const uint4* x, int N, int K, int R, floa
   auto tile_groups = [&](int n) { return std::max(1, std::min(wgs(n) / a.SK, a.n_tiles)); };
   auto tiles = [&](int n) { return (a.n_tiles + tile_groups(n) - 1) / tile_groups(n); };
   int rg = (nrt + most - 1) / most, mt = (nrt + rg - 1) / rg;
-  for (int n = rg + 1, t = tiles(rg); (nrt + n - 1) / n >= 3 && tiles(n) <= t; ++n) mt = (nrt + n - 1) / n;
+  for (int n = rg + 1, t = tiles(rg); (nrt + n - 1) / n >= 3 && n * wgs(n) <= 256 && tiles(n) <= t; ++n)
+    mt = (nrt + n - 1) / n;
   rg = (nrt + mt - 1) / mt;
   a.G = tile_groups(rg);
   if (rg == 1) {
@@ -815,7 +817,9 @@ inline bool wide_block(int R, int S, int n_items, int epi) {
   if (R <= (S > 64 || epi == EP_ROPE || epi == EP_STORE ? 2 * FK_GROUP + 1 : 192)) return false;
   const int per = epi == EP_ROPE || epi == EP_SWIGLU ? 2 : 1;
   const WidePlan p = wide_plan<DT>(R, per * n_items, S, epi);
-  const int P = fk_group_wgs(fk_groups(R)), tiles = (n_items + P - 1) / P * per;
+  // (groups past 32 are more workgroups than CUs: in turns)
+  const int ng = fk_groups(R), P = fk_group_wgs(ng), turns = (ng * P + 255) / 256;
+  const int tiles = (n_items + P - 1) / P * per * turns;
   int Sg = GEMM_WAVES;
   while (Sg < S) Sg *= 2;
   if (DT == DT_F32) return 2 * p.rounds * p.mt * p.nt * S <= 7 * tiles * Sg - (epi == EP_SWIGLU ? 8 * S : 0);

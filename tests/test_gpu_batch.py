@@ -84,6 +84,28 @@ def test_batch_rows_equal_single_sequence_rows_bitwise(ee, tree):
     eng.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_batch_of_2080_rows_equals_single_sequence_rows_bitwise(ee, dtype):
+    """32 sequences of 65 rows: 130 row tiles, more than the row groups that
+    give every workgroup a CU (26 groups of five row tiles in the bf16 down
+    projection, against one of five for a sequence alone)."""
+    shape = _bf16_small() if dtype == "bf16" else get_shape("tiny")
+    w = gen_weights(shape, seed=52, std=0.05)
+    B, K = 32, 64
+    eng, _ = _engine(ee, shape, w, [zipf_tokens(shape.vocab, 20 + 3 * i, seed=160 + i) for i in range(B)], max_ctx=256)
+    drafts = [zipf_tokens(shape.vocab, K, seed=200 + b) for b in range(B)]
+    states = [eng.seq_state(b) for b in range(B)]
+    single, logits = [], []
+    for b in range(B):
+        single.append(eng.verify(b, drafts[b])[:2])
+        logits.append(eng.logits())
+        eng.rollback(b, *states[b])
+    res = eng.verify_batch(list(range(B)), drafts)
+    assert [r[:2] for r in res] == single
+    np.testing.assert_array_equal(eng.logits(), np.concatenate(logits))
+    eng.close()
+
+
 def test_batch_reuse_sessions_match_oracle(ee):
     """Three tiny fp32 Reuse sessions advanced together, each against its own
     oracle session."""
