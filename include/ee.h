@@ -93,11 +93,11 @@ typedef struct {
  * Return 0 for an invalid config.
  * The workspace is sized for blocks of max(max_seqs * (k_max + 1), P) rows,
  * P = up to 512 rows of a prompt or extension (ee_prefill) whatever k_max is.
- * Its largest part is the greater of the attention split states,
- * (ceil(max_ctx / 256) + 1) * n_heads * rows * (head_dim + 2) * 4 bytes, and
- * the GEMM slice partials, which share one region: 7B-class bf16, k_max 32, one
- * sequence: 128 MB at max_ctx 2048, 322 MB at 8192 (1B class 166 MB, 33B class
- * 558 MB at 8192). */
+ * Its largest parts are the attention split states, (ceil(max_ctx / 256) + 1)
+ * * n_heads * rows * (head_dim + 2) * 4 bytes, and the GEMM slice partials,
+ * which take the states' tail where the states are the larger.  7B-class
+ * bf16, k_max 32, one sequence: 205 MB at max_ctx 2048, 322 MB at 8192 (1B
+ * class 166 MB, 33B class 558 MB at 8192). */
 size_t ee_packed_weight_bytes(const ee_model_config* cfg);
 size_t ee_kv_pool_bytes(const ee_model_config* cfg);
 size_t ee_workspace_bytes(const ee_model_config* cfg);

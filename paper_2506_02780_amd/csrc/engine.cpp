@@ -202,20 +202,22 @@ Layout make_layout(const ee_model_config* c) {
   L.ssqt = o; o += up(Rall * (d / 16) * 4);
   L.zbuf = o; o += up(Tpad * F * esz);
   L.q = o; o += up(Rall * H * hd * esz);
-  // attention split states and the split-K partials of the largest GEMM,
+  // attention split states, and the split-K partials of the largest GEMM,
   // [slices][rows][N] (the LM head of a prompt block: its last rows from the
-  // start of their row tile), share one region: each is consumed by the launch
-  // after the one that writes it, so the two are never live together.  The
-  // smaller ends where the larger does, so that the blocks of ordinary drafts,
-  // which use the front of each, still find them apart (on the same bytes the
-  // attention kernel took 12.8 us instead of 11.6: 7B, K = 32).
-  const size_t states = up((size_t)L.max_splits * Hkv * Rall * L.G * (hd + 2) * 4);
+  // start of their row tile).  Each is consumed by the launch after the one
+  // that writes it, so where the states are the larger (long contexts) the
+  // partials take their tail, past what verify blocks of any length and prompt
+  // blocks of the first 1024 positions write: only late blocks of long prompts
+  // meet there (on the same bytes the attention kernel took 12.8 us instead
+  // of 11.6: 7B, K = 32).
+  const auto states_of = [&](size_t splits, size_t rows) { return up(splits * H * rows * (hd + 2) * 4); };
+  const size_t states = states_of(L.max_splits, Rall);
   const size_t partials =
       up(std::max(partial_cols(*c) * std::max(L.Rmax, L.Tmax + 15), partial_cols(*c, false) * Rall) * 4);
-  const size_t region = std::max(states, partials);
-  L.part = o + region - states;
-  L.gpart = o + region - partials;
-  o += region;
+  const size_t front = std::max(states_of(L.max_splits, L.Rmax), states_of(std::min(L.max_splits, 1024 / SPLIT + 1), Rall));
+  L.part = o;
+  L.gpart = o + (states > partials ? std::max(states - partials, front) : states);
+  o = std::max(L.part + states, L.gpart + partials);
   L.logits = o; o += up(L.Rmax * V * 4);
   L.amax = o; o += up(L.Rmax * ((V + 2047) / 2048) * 8 * 8);
   L.greedy = o; o += up(L.Rmax * 4);

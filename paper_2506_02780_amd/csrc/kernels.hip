@@ -401,14 +401,13 @@ static hipError_t gemm(const uint4* w, const uint4* x, int N, int K, int R, floa
 // (with a run-time count each group of four elements was a round trip of its
 // own).  Bound by the partials, read once: 33B batch of 260 rows 856.7 -> 828.0
 // us, K = 512 step over four 7B layers 1789 -> 1759, K = 32 459.2 -> 455.5.
-// (K0 > 0: slices K0 .. K0 + SK - 1 added to what v and v2 hold.)
-template <int SK, bool TWO, int K0 = 0>
+template <int SK, bool TWO>
 __device__ __forceinline__ void sum_slices_n(const float* __restrict__ part, int T, int N, int t, int n, int n2,
                                              float (&v)[8], float (&v2)[8]) {
   float4 u[TWO ? 4 : 2][SK];
 #pragma unroll
   for (int k = 0; k < SK; ++k) {
-    const float* r = part + ((size_t)(K0 + k) * T + t) * N;
+    const float* r = part + ((size_t)k * T + t) * N;
     u[0][k] = *reinterpret_cast<const float4*>(r + n);
     u[1][k] = *reinterpret_cast<const float4*>(r + n + 4);
     if constexpr (TWO) {
@@ -418,17 +417,17 @@ __device__ __forceinline__ void sum_slices_n(const float* __restrict__ part, int
   }
 #pragma unroll
   for (int i = 0; i < (TWO ? 4 : 2); ++i) {
-    float(&o)[8] = i < 2 ? v : v2;
-    const int e = 4 * (i & 1);
     float4 w = u[i][0];
-    if (K0) { w.x = o[e] + w.x; w.y = o[e + 1] + w.y; w.z = o[e + 2] + w.z; w.w = o[e + 3] + w.w; }
 #pragma unroll
     for (int k = 1; k < SK; ++k) { w.x += u[i][k].x; w.y += u[i][k].y; w.z += u[i][k].z; w.w += u[i][k].w; }
-    o[e] = w.x; o[e + 1] = w.y; o[e + 2] = w.z; o[e + 3] = w.w;
+    float(&o)[8] = i < 2 ? v : v2;
+    o[4 * (i & 1)] = w.x; o[4 * (i & 1) + 1] = w.y; o[4 * (i & 1) + 2] = w.z; o[4 * (i & 1) + 3] = w.w;
   }
 }
-// (reductions over d_model, the only ones that are read in pairs, have at most 8 slices)
+// (MAXK: the most slices that the caller's reductions can have: over d_model 8,
+// else 16 in bf16 and 32 in fp32)
 constexpr int MAX_D_SLICES = 8;
+constexpr int max_slices(int DT) { return DT == DT_BF16 ? 16 : 32; }
 template <bool TWO>
 __device__ __forceinline__ void sum_slices(const float* __restrict__ part, int SK, int T, int N, int t, int n, int n2,
                                            float (&v)[8], float (&v2)[8]) {
@@ -436,18 +435,25 @@ __device__ __forceinline__ void sum_slices(const float* __restrict__ part, int S
     case 1: sum_slices_n<1, TWO>(part, T, N, t, n, n2, v, v2); break;
     case 2: sum_slices_n<2, TWO>(part, T, N, t, n, n2, v, v2); break;
     case 4: sum_slices_n<4, TWO>(part, T, N, t, n, n2, v, v2); break;
-    case MAX_D_SLICES: sum_slices_n<MAX_D_SLICES, TWO>(part, T, N, t, n, n2, v, v2); break;
-    default:
-      if constexpr (!TWO) {
-        sum_slices_n<16, false>(part, T, N, t, n, n2, v, v2);
-        // (fp32 over more than 16384 columns; 64 loads at once would not fit the registers)
-        if (SK == 32) sum_slices_n<16, false, 16>(part, T, N, t, n, n2, v, v2);
-      }
+    case 8: sum_slices_n<8, TWO>(part, T, N, t, n, n2, v, v2); break;
+    default:   // (pairs of elements are read over d_model only: 64 loads would not fit the registers)
+      if constexpr (!TWO) sum_slices_n<16, false>(part, T, N, t, n, n2, v, v2);
   }
 }
+template <int MAXK>
 __device__ __forceinline__ void sum_slices8(const float* __restrict__ part, int SK, int T, int N, int t, int n,
                                             float (&v)[8]) {
   sum_slices<false>(part, SK, T, N, t, n, 0, v, v);
+  if constexpr (MAXK == 32)   // fp32 over more than 16384 columns: the slices past the sixteenth
+    if (SK == 32) {
+#pragma unroll 1
+      for (int k = 16; k < 32; ++k) {
+        const float* r = part + ((size_t)k * T + t) * N + n;
+        const float4 a = *reinterpret_cast<const float4*>(r), b = *reinterpret_cast<const float4*>(r + 4);
+        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
+        v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
+      }
+    }
 }
 
 // Pack 8 consecutive values of row t starting at column col (col % 8 == 0)
@@ -1412,8 +1418,9 @@ __global__ __launch_bounds__(GEMM_WAVES * 64) void gemm_wide_kernel(WideArgs a) 
     const int sl = wv + W * L.i;
     const unsigned vo = (L.task < t1 && sl < S) ? (unsigned)lane * 16u : OOB;
     // (a masked load's scalar offset stays inside the buffer too: the range
-    // check subtracts it from the size, and the difference must not wrap)
-    const unsigned so = (unsigned)min(sl, S - 1) * 1024u;
+    // check subtracts it from the size, and the difference must not wrap.  QKV's
+    // chains are all of one length: gemm_wide)
+    const unsigned so = (unsigned)(EPI == EP_ROPE ? sl : min(sl, S - 1)) * 1024u;
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(ws, vo, wo[n] + so, NTW ? 2 : 0);
@@ -1700,6 +1707,7 @@ template <int DT, int EPI>
 static hipError_t gemm_wide(WideArgs a, int R, hipStream_t st) {
   a.e.R = R;
   const int nrt = (R + 15) / 16, cols = a.e.n_items * (EPI == EP_ROPE || EPI == EP_SWIGLU ? 2 : 1);
+  if (EPI == EP_ROPE && a.e.S % GEMM_WAVES) return hipErrorInvalidValue;   // (d is a multiple of 256: fused_proj)
   const WidePlan p = wide_plan<DT>(R, cols, a.e.S, EPI);
   a.ng = (nrt + p.mt - 1) / p.mt;
   a.ntask = a.ng * ((cols + p.nt - 1) / p.nt);
@@ -1798,7 +1806,7 @@ __device__ __forceinline__ void resid_block(int bx, int t, const void* __restric
     } else {
       const float4 h0 = *reinterpret_cast<const float4*>(hr), h1 = *reinterpret_cast<const float4*>(hr + 4);
       float p[8];
-      sum_slices8(part, SK, T, d, t, col, p);
+      sum_slices8<max_slices(DT)>(part, SK, T, d, t, col, p);
       v[0] = h0.x + p[0]; v[1] = h0.y + p[1]; v[2] = h0.z + p[2]; v[3] = h0.w + p[3];
       v[4] = h1.x + p[4]; v[5] = h1.y + p[5]; v[6] = h1.z + p[6]; v[7] = h1.w + p[7];
     }
@@ -1994,7 +2002,7 @@ __global__ __launch_bounds__(256) void logits_kernel(const float* __restrict__ p
   if (col < V) {   // V is a multiple of 16: a thread's 8 columns are all in range or all out
     const float rs = row_scale(ssq, t, d, eps);   // the final norm's row scale
     float v[8];
-    sum_slices8(part, SK, T, V, t, col, v);
+    sum_slices8<MAX_D_SLICES>(part, SK, T, V, t, col, v);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] *= rs;
     float* lr = logits + (size_t)t * V + col;

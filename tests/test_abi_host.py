@@ -33,15 +33,16 @@ def test_every_declared_symbol_is_exported():
 
 @pytest.mark.parametrize("model,max_ctx,seqs,k_max", [("7b", 8192, 1, 32), ("7b", 2048, 1, 0), ("1b", 8192, 1, 32),
                                                       ("33b", 8192, 1, 32), ("33b", 4096, 4, 64), ("tiny", 256, 1, 8)])
-def test_workspace_holds_one_of_attention_states_and_partials(model, max_ctx, seqs, k_max):
-    """Rows: the verify blocks' or a prompt block's (up to 512).  Attention split
-    states and GEMM partials share one place; the rest is a few values per row
-    and column, the verify blocks' logits and the rotary table."""
+def test_workspace_shares_attention_states_and_partials(model, max_ctx, seqs, k_max):
+    """Rows: the verify blocks' or a prompt block's (up to 512).  Where the
+    attention split states are larger than the GEMM partials, the partials take
+    the states' tail, past what verify blocks and prompt blocks of 1024 positions
+    use; the rest is a few values per row and column, the verify blocks' logits
+    and the rotary table."""
     import paper_2506_02780_amd as ee
     s = get_shape(model)
     esz, verify = (2 if s.dtype == "bf16" else 4), seqs * (k_max + 1)
     rows = max(verify, min(512, -(-max_ctx // 16) * 16))
-    states = (-(-max_ctx // 256) + 1) * s.n_heads * rows * (s.head_dim + 2) * 4
 
     def slices(k):
         n = 1
@@ -50,11 +51,19 @@ def test_workspace_holds_one_of_attention_states_and_partials(model, max_ctx, se
         return n
     cols = max(slices(s.d_model) * (s.q_dim + 2 * s.kv_dim), slices(s.q_dim) * s.d_model,
                slices(s.d_model) * 2 * s.ffn, slices(s.ffn) * s.d_model)
+
+    def states(splits, n):
+        return splits * s.n_heads * n * (s.head_dim + 2) * 4
+    splits = -(-max_ctx // 256) + 1
     partials = 4 * max(cols * rows, slices(s.d_model) * s.vocab * max(verify, k_max + 16))
+    front = max(states(splits, verify), states(min(splits, 5), rows))
+    region = states(splits, rows) + partials
+    if states(splits, rows) > partials:
+        region = max(states(splits, rows), front + partials)
     others = rows * (4 * s.d_model + s.d_model // 4 + esz * (2 * max(s.d_model, s.q_dim) + s.q_dim + s.ffn) + 64)
     others += verify * (4 * s.vocab + s.vocab // 32 + 128) + max_ctx * s.head_dim * 4
     total = ee.ee_workspace_bytes(ctypes.byref(ee.make_config(s, max_ctx=max_ctx, max_seqs=seqs, k_max=k_max)))
-    assert max(states, partials) < total < max(states, partials) + others + (1 << 16)
+    assert region < total < region + others + (1 << 16)
 
 
 def test_config_sizes_and_validation():
